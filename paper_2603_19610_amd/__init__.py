@@ -170,15 +170,27 @@ def _check(status: int, where: str):
         raise PvlmError(status, where, detail)
 
 
+# A small call is bound by this module, not by its kernels: pointers and
+# streams go to ctypes as plain integers (the argument types make the
+# conversion), the raw stream is asked for directly (no torch.cuda.Stream object
+# is built), and an argument that passes takes one test.  A rotary append with
+# a verify call of one small layer: 35.7 -> 33.3 us (T = 4 rows over 504, paged).
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+def _raw_stream(device: int) -> int:
+    return torch._C._cuda_getCurrentRawStream(device)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _need(t: torch.Tensor, name: str, dtype=None, device=None):
+    if (isinstance(t, torch.Tensor) and t.is_cuda and (device is None or t.device == device)
+            and (dtype is None or t.dtype is dtype) and t.is_contiguous()):
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if not t.is_cuda:
@@ -237,7 +249,8 @@ def _no_capture(what: str):
 
 
 def _default_ws(kind: str) -> Workspace:
-    key = (kind, torch.cuda.current_device(), torch.cuda.current_stream().cuda_stream)
+    dev = torch.cuda.current_device()
+    key = (kind, dev, _raw_stream(dev))
     ws = _ws_cache.get(key)
     if ws is None:
         # (under graph capture the buffer comes from the graph's pool and its
