@@ -46,14 +46,16 @@
  *     in flight at the same time.  The library's only mutable state is the
  *     per-stream compute-unit budgets below and the fixed scratch of
  *     pvlm_verify_attn_noalloc.
- *   - Workgroups that wait on each other.  pvlm_verify_attn(_paged), top-k
- *     rows longer than 16384 scores and pvlm_spec_accept split their work
- *     over workgroups of one launch that exchange partial results and wait
- *     for each other (bounded waits: a wait that gives up sets
- *     PVLM_DEV_TIMEOUT, and the results are invalid).  Every workgroup must
- *     therefore be resident at once.  Each call checks before launching that
- *     its grid fits the device (the runtime's occupancy per compute unit
- *     times the compute units it plans for; PVLM_ERR_UNSUPPORTED otherwise).
+ *   - Workgroups that wait on each other.  pvlm_verify_attn(_paged) with mass
+ *     while its stream is captured, top-k rows longer than 16384 scores and
+ *     pvlm_spec_accept split their work over workgroups of one launch that
+ *     exchange partial results and wait for each other (bounded waits: a wait
+ *     that gives up sets PVLM_DEV_TIMEOUT, and the results are invalid).
+ *     Every workgroup must therefore be resident at once.  Each call checks
+ *     before launching that its grid fits the device (the runtime's occupancy
+ *     per compute unit times the compute units it plans for; a verify call
+ *     whose grid does not fit runs without waits, the others return
+ *     PVLM_ERR_UNSUPPORTED).  Eager verify calls never wait.
  *     Eager launches on a stream without a budget are cooperative launches,
  *     whose co-residency the runtime guarantees.  Launches captured into a
  *     graph, and launches on a budgeted stream, are ordinary launches: then
@@ -71,10 +73,10 @@
  *     unit at most; budgets are multiples of the XCD count, so a grid spreads
  *     evenly over the XCDs the device deals workgroups to in turn).
  *   - Workspaces: zero-fill a workspace once before its first use.  Its first
- *     1 MiB holds the counters of the waits between workgroups, and every
- *     call leaves them in a consistent state (zero again, or, for verify's
- *     monotonic counters, advanced together), so one buffer (at least as large
- *     as each call requires) serves calls of any kind and shape in sequence.
+ *     1 MiB holds the words of the waits between workgroups, and every call
+ *     leaves them in a consistent state (zero again, or, for monotonic
+ *     counters, advanced together), so one buffer (at least as large as each
+ *     call requires) serves calls of any kind and shape in sequence.
  *   - Layouts are C-contiguous, innermost index last.  "bf16" is IEEE
  *     bfloat16 stored in 2 bytes.
  */
@@ -112,8 +114,8 @@ typedef enum {
 #define PVLM_DEV_RANGE 1    /* a device-resident size or index was out of range */
 #define PVLM_DEV_TIMEOUT 2  /* an inter-workgroup wait gave up (results invalid;
                                zero-fill the workspace again before reusing it) */
-#define PVLM_DEV_PLACEMENT 4 /* a workgroup ran on another XCD than the launch
-                               planned for (results may be invalid)          */
+#define PVLM_DEV_PLACEMENT 4 /* reserved: a workgroup ran on another XCD than
+                               the launch planned for (no call raises it)    */
 
 /* Compute-unit budget of `stream` on the current device: cus = 0 removes it
  * (calls then plan for the whole device), otherwise a multiple of the

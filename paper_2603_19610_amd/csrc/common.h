@@ -41,11 +41,12 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // the inter-workgroup waits, so a zero-filled workspace can be reused by calls
 // of any shape: their data areas (after the region) may overlap earlier data,
 // their counters never do.  Calls whose counters return to zero use the low
-// part of the region; monotonic counters (each call leaves them consistent,
-// never resets them) use the rest: verify's from kSyncMonoOff, top-k's from
-// kSyncTopkOff (one line per batch row), accept's at kSyncAcceptOff.
+// part of the region.  Verify's statistics records that a launch waits on
+// (0 between calls) lie from kSyncVerifyOff; top-k's monotonic counters (each
+// call leaves them consistent, never resets them) from kSyncTopkOff (one line
+// per batch row), accept's at kSyncAcceptOff.
 constexpr size_t kSyncRegion = 1024 * 1024;
-constexpr size_t kSyncMonoOff = 256 * 1024;
+constexpr size_t kSyncVerifyOff = 256 * 1024;
 constexpr size_t kSyncTopkOff = 768 * 1024;
 constexpr size_t kSyncAcceptOff = 896 * 1024;
 // Counters that many workgroups update or poll get a 128-byte line each, so
@@ -126,53 +127,6 @@ __device__ __forceinline__ void st_agent(int* p, int v) {
 // wave always exits.
 constexpr int kSpinLimit = 1 << 20;
 
-// Inter-workgroup exchange protocol.  Data another workgroup will read is
-// written with st_agent (device-coherent stores) and read with ld_agent
-// (device-coherent loads).  A workgroup signals with wg_signal*: every wave
-// first waits for its own memory operations to complete (s_waitcnt 0, after
-// which its coherent stores are visible device-wide), then thread 0 bumps the
-// counter with a relaxed atomic.  Waiters poll with relaxed atomic loads.  No
-// cache-wide fence is needed because no exchanged datum ever lives only in a
-// non-coherent cache.
-// `writer_wave0` limits the completion wait to wave 0 when only wave 0 wrote
-// data other workgroups will read (the other waves may keep loads in flight).
-__device__ __forceinline__ void wg_signal_wait(int* counter, int target, int32_t* status,
-                                               bool wait, bool writer_wave0 = false) {
-  // wave-uniform (scalar) branch: an exec-masked one would still run the wait
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  if (!writer_wave0 || wave == 0) __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (wait) {
-      int spins = 0;
-      while (__hip_atomic_load(counter, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-        __builtin_amdgcn_s_sleep(1);
-        if (++spins > kSpinLimit) {
-          dev_flag(status, PVLM_DEV_TIMEOUT);
-          break;
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
-// Signal without waiting; true in every thread of the workgroup whose signal
-// brought the counter to `target` (the last arriver).  `s_flag` is a
-// __shared__ int.
-__device__ __forceinline__ bool wg_signal_last(int* counter, int target, int* s_flag) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  if (threadIdx.x == 0)
-    *s_flag = __hip_atomic_fetch_add(counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-              target - 1;
-  __syncthreads();
-  const bool last = *s_flag != 0;
-  __syncthreads();
-  return last;
-}
-
 // Workgroup barrier that orders LDS only: global loads and stores stay in
 // flight across it (a full __syncthreads waits for every outstanding memory
 // operation of the wave first).
@@ -210,34 +164,6 @@ __device__ __forceinline__ void grp_poll(const unsigned* counter, unsigned targe
       break;
     }
   }
-}
-
-// Stores and loads of data exchanged between workgroups.  LOCAL: every
-// workgroup of the exchange runs on one XCD and so shares one L2; data is
-// written and read once per launch at addresses the reader has not touched
-// before in the launch (its L1 holds no copy), so plain accesses through that
-// L2 are coherent.  Otherwise device-coherent accesses are used.
-template <bool LOCAL>
-__device__ __forceinline__ void x_store(float* p, float v) {
-  if constexpr (LOCAL) *p = v; else st_agent(p, v);
-}
-template <bool LOCAL>
-__device__ __forceinline__ void x_store(uint64_t* p, uint64_t v) {
-  if constexpr (LOCAL) *p = v;
-  else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <bool LOCAL>
-__device__ __forceinline__ void x_store(float2* p, float2 v) {
-  if constexpr (LOCAL) *p = v; else st_agent(p, v);
-}
-template <bool LOCAL>
-__device__ __forceinline__ float2 x_load(const float2* p) {
-  if constexpr (LOCAL) return *p; else return ld_agent(p);
-}
-template <bool LOCAL>
-__device__ __forceinline__ uint64_t x_load(const uint64_t* p) {
-  if constexpr (LOCAL) return *p;
-  else return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // The cache rows of one (batch, KV head): contiguous (base = the head's row
