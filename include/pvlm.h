@@ -47,14 +47,14 @@
  *     per-stream compute-unit budgets below and the fixed scratch of
  *     pvlm_verify_attn_noalloc.
  *   - Workgroups that wait on each other.  pvlm_verify_attn(_paged) with mass
- *     while its stream is captured, top-k rows longer than 16384 scores and
- *     pvlm_spec_accept split their work over workgroups of one launch that
- *     exchange partial results and wait for each other (bounded waits: a wait
- *     that gives up sets PVLM_DEV_TIMEOUT, and the results are invalid).
+ *     while its stream is captured, and top-k rows longer than 16384 scores,
+ *     split their work over workgroups of one launch that exchange partial
+ *     results and wait for each other (bounded waits: a wait that gives up
+ *     sets PVLM_DEV_TIMEOUT, and the results are invalid).
  *     Every workgroup must therefore be resident at once.  Each call checks
  *     before launching that its grid fits the device (the runtime's occupancy
  *     per compute unit times the compute units it plans for; a verify call
- *     whose grid does not fit runs without waits, the others return
+ *     whose grid does not fit runs without waits, top-k returns
  *     PVLM_ERR_UNSUPPORTED).  Eager verify calls never wait.
  *     Eager launches on a stream without a budget are cooperative launches,
  *     whose co-residency the runtime guarantees.  Launches captured into a
@@ -469,7 +469,7 @@ pvlm_status pvlm_gather_kv_paged(pvlm_dtype dt, int n_layers, int B, int Hkv, in
  *   near_tie (nullable) [B]: 1 when a decision or the draw fell within 1e-9
  *   (relative) of its boundary, where another summation order could flip it.
  * Limits: B <= 256, gamma <= 32, V <= 1048576 (PVLM_ERR_UNSUPPORTED).  The
- * workgroups of the one launch exchange partial sums through `ws`
+ * call's launches pass partial sums through `ws`
  * (pvlm_spec_accept_workspace_size bytes, zero-filled before first use).
  * ---------------------------------------------------------------------- */
 size_t pvlm_spec_accept_workspace_size(int B, int gamma, int V);

@@ -2,24 +2,27 @@
 // with probability min(1, p/q); on rejection draw from norm(max(0, p - q)))
 // and the bonus token after full acceptance (Suppl. B).
 //
-// One cooperative launch of 512-thread workgroups, three phases separated by
-// two grid-wide waits:
-//  1. every (batch, row, vocabulary chunk) item: the chunk's max (lowest
-//     argmax) and sum of exp((z - max) / temperature) in float64, from one
-//     coalesced read of the chunk held in registers;
-//  2. every workgroup with draw work combines the chunk results of its batch
-//     into each row's max and normaliser, evaluates the accept test of every
-//     drafted position in parallel (float64) and takes the first rejection a,
-//     then computes the mass of its small chunk of the draw distribution (the
-//     residual max(0, p_a - q_a), or p_gamma for the bonus), keeping the
-//     values; the draw chunks are spread over the whole grid;
-//  3. after the second wait every such workgroup scans the chunk masses to
-//     locate the chunk where the cumulative mass first exceeds u' * total;
-//     that chunk's workgroup scans its kept values and writes the outputs.
-// temperature == 0 stops after the first wait (greedy argmax).
+// Three ordinary launches of 512-thread workgroups; the kernel boundaries take
+// the place of grid-wide waits, so no launch is cooperative and none holds
+// compute units while it waits:
+//  1. stats: every (batch, row, vocabulary chunk) item: the chunk's max
+//     (lowest argmax) and sum of exp((z - max) / temperature) in float64, from
+//     one coalesced read of the chunk held in registers;
+//  2. mass: every (batch, draw chunk) item combines the chunk results of its
+//     batch into each row's max and normaliser, evaluates the accept test of
+//     every drafted position in parallel (float64) and takes the first
+//     rejection a, then sums its small chunk of the draw distribution (the
+//     residual max(0, p_a - q_a), or p_gamma for the bonus);
+//  3. pick: one workgroup per batch row scans the chunk masses for the chunk
+//     where the cumulative mass first exceeds u' * total, forms that chunk's
+//     values again and writes the outputs.
+// temperature == 0 stops after the decisions (greedy argmax).
 //
-// The waits: see grid_wait (no end-of-kernel round trip returns anything to
-// zero).
+// Latency-bound: 8 drafts x 152064 entries are 10 MB (2 us).  One launch with
+// two grid-wide waits took 38.5 us a pass eagerly (~16 of them the cooperative
+// launch's own) and 21.0 captured; the three take 19.0 and 18.9.  Batch of
+// four: 57.3 and 40.6 against 36.6 and 37.0, 22 of them the float64
+// exponentials of the statistics.
 #include "common.h"
 
 namespace pvlm {
@@ -43,6 +46,12 @@ constexpr double kNegInfD = -__builtin_huge_val();
 // Inputs, then sizes, then outputs and workspace: the argument loads merge
 // adjacent fields into wide scalar loads allocated (and spilled) as one
 // unit, so fields used at different times sit in separate runs.
+// What the accept tests of a batch row decided.
+struct Decision {
+  int acc, tie;
+  double pM, pZ, qM, qZ;
+};
+
 struct AArgs {
   const float* dl;
   const float* tl;
@@ -62,53 +71,12 @@ struct AArgs {
   int* pi;          // [B][RW][NC] chunk argmax (lowest index)
   double* rs;       // [B][ND] residual mass of each draw chunk
   double* qs;       // [B][ND] p mass of each draw chunk (used when the residual is empty)
-  int* arrive;      // [2][kArriveSets + 1] arrival counters of the two waits (128 bytes apart), zero at rest
-  unsigned* gen;    // [kArriveSets] generation words (128 bytes apart), advanced once per wait
+  Decision* dec;    // [B] what the mass kernel decided
 };
 
 __device__ __forceinline__ const float* row_ptr(const AArgs& a, int b, int rho) {
   if (rho <= a.gamma) return a.tl + ((size_t)b * (a.gamma + 1) + rho) * a.V;
   return a.dl + ((size_t)b * a.gamma + (rho - a.gamma - 1)) * a.V;
-}
-
-// Grid-wide wait `p` (0 or 1): arrive, and (if `wait`) wait for every
-// workgroup's arrival.  The workgroups form eight sets (by index mod 8).
-// Arrivals go to their set's counter, so no counter line takes more than an
-// eighth of the grid's atomics (same-line atomics serialise); the last
-// arrival of each set counts it at a second counter, and the last of those
-// advances the generation word, one copy per set, which the set's others
-// poll (polling a counter itself would slow the arrivals down).  Every
-// counter returns to zero when its last arrival has seen it.  The generation
-// is never reset: every workgroup reads its set's copy at its start, before
-// its first arrival, so wait p releases at that value + p + 1.
-constexpr int kArriveSets = 8;
-__device__ __forceinline__ unsigned* gen_word(const AArgs& a) {
-  return a.gen + (blockIdx.x % kArriveSets) * (kSyncLine / sizeof(unsigned));
-}
-__device__ void grid_wait(const AArgs& a, int p, unsigned g0, bool wait) {
-  __builtin_amdgcn_s_waitcnt(0);  // this workgroup's published data is visible
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    constexpr int kLineI = (int)(kSyncLine / sizeof(int));
-    int* base = a.arrive + p * (kArriveSets + 1) * kLineI;
-    const int set = (int)(blockIdx.x % kArriveSets);
-    const int members = ((int)gridDim.x - set + kArriveSets - 1) / kArriveSets;
-    const int sets = (int)gridDim.x < kArriveSets ? (int)gridDim.x : kArriveSets;
-    bool released = false;
-    int* c1 = base + set * kLineI;
-    if (__hip_atomic_fetch_add(c1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == members - 1) {
-      reset_counter(c1);
-      int* c2 = base + kArriveSets * kLineI;
-      if (__hip_atomic_fetch_add(c2, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sets - 1) {
-        reset_counter(c2);
-        for (int k = 0; k < kArriveSets; ++k)
-          __hip_atomic_store(a.gen + k * kLineI, g0 + (unsigned)p + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        released = true;
-      }
-    }
-    if (!released && wait) grp_poll(a.gen + set * kLineI, g0 + (unsigned)p + 1u, a.status);
-  }
-  __syncthreads();
 }
 
 // Exclusive scans of two doubles per thread over the workgroup (fixed order,
@@ -262,38 +230,101 @@ __device__ __forceinline__ int strided_index(int y0, int j) {
   return y0 + 4 * ((j / 4) * kAccThreads + (int)threadIdx.x) + (j % 4);
 }
 
-// Per-batch state every draw workgroup derives after the first wait.
-struct Decision {
-  int acc, tie;
-  double pM, pZ, qM, qZ;
-};
-
-template <bool VEC, int kDrawPer>
-__global__ void __launch_bounds__(kAccThreads) accept_kernel(AArgs a) {
-  constexpr int kDrawChunk = kAccThreads * kDrawPer;
+template <bool VEC>
+__global__ void __launch_bounds__(kAccThreads) accept_stats_kernel(AArgs a) {
   __shared__ float s_fv[kAccWaves];
   __shared__ int s_fi[kAccWaves];
+  __shared__ double s_d[kAccWaves];
+  const int tid = threadIdx.x;
+  const int RW = 2 * a.gamma + 1;
+  const double inv_tau = a.greedy ? 0.0 : 1.0 / a.tau;
+  // chunk max / argmax / exp-sum (greedy: target rows only)
+  const int rows1 = a.greedy ? a.gamma + 1 : RW;
+  const int it = blockIdx.x;
+  const int c = it % a.NC, rho = (it / a.NC) % rows1, b = it / (a.NC * rows1);
+  const size_t slot = ((size_t)b * RW + rho) * a.NC + c;
+  const float* z = row_ptr(a, b, rho);
+  const int y0 = c * kChunk, y1 = min(a.V, y0 + kChunk);
+  float v[kAccPer];
+  load_strided<VEC>(z, y0, y1, v);
+  float mx = -INFINITY;
+  int am = 0x7fffffff;
+#pragma unroll
+  for (int j = 0; j < kAccPer; ++j)
+    if (v[j] > mx) {  // ascending index order within the thread: first max kept
+      mx = v[j];
+      am = strided_index(y0, j);
+    }
+  block_argmax(mx, am, s_fv, s_fi);
+  double sum = 0.0;
+  if (!a.greedy && mx != -INFINITY) {
+    // no branches around the exponentials (entries past the chunk are -inf
+    // and contribute exp(-inf) = 0), so their evaluations interleave
+    const double M = mx;
+    double e[kAccPer];
+#pragma unroll
+    for (int j = 0; j < kAccPer; ++j) e[j] = exp(((double)v[j] - M) * inv_tau);
+#pragma unroll
+    for (int j = 0; j < kAccPer; ++j) sum += e[j];
+  }
+  sum = block_sum(sum, s_d);
+  if (tid == 0) {
+    a.pm[slot] = mx == -INFINITY ? kNegInfD : (double)mx;
+    a.ps[slot] = sum;
+    a.pi[slot] = am;
+  }
+}
+
+// Entries y = c * kDrawChunk + kDrawPer * tid + j of draw chunk c: r(y) of the
+// draw distribution (the residual max(0, p - q), or p for the bonus) or, with
+// want_p, p(y); returns this thread's sum of p(y) as well.
+template <int kDrawPer>
+__device__ double draw_values(const AArgs& a, const Decision& d, int b, int c, bool want_p, double (&r)[kDrawPer]) {
+  constexpr int kDrawChunk = kAccThreads * kDrawPer;
+  const int tid = threadIdx.x;
+  const double inv_tau = 1.0 / a.tau;
+  const bool resid = !want_p && d.acc < a.gamma;
+  const double ipz = 1.0 / d.pZ, iqz = 1.0 / d.qZ;
+  const float* zpr = row_ptr(a, b, d.acc);
+  const float* zqr = row_ptr(a, b, a.gamma + 1 + min(d.acc, a.gamma - 1));
+  const int y = c * kDrawChunk + kDrawPer * tid;
+  float zp[kDrawPer], zq[kDrawPer];
+#pragma unroll
+  for (int j = 0; j < kDrawPer; ++j) {
+    // clamped loads, all in flight together; past V: p = 0, q = 0
+    const float xp = zpr[min(y + j, a.V - 1)], xq = zqr[min(y + j, a.V - 1)];
+    zp[j] = y + j < a.V ? xp : -INFINITY;
+    zq[j] = y + j < a.V && resid ? xq : -INFINITY;
+  }
+  double psum = 0.0;
+#pragma unroll
+  for (int j = 0; j < kDrawPer; ++j) {
+    const double p = exp(((double)zp[j] - d.pM) * inv_tau) * ipz;
+    const double q = exp(((double)zq[j] - d.qM) * inv_tau) * iqz;
+    psum += p;
+    r[j] = !resid ? p : (p > q ? p - q : 0.0);
+  }
+  return psum;
+}
+
+template <int kDrawPer>
+__global__ void __launch_bounds__(kAccThreads) accept_mass_kernel(AArgs a) {
   __shared__ double s_d[2 * kAccWaves];
   __shared__ double s_M[kMaxRows], s_Z[kMaxRows];
   __shared__ int s_arg[kMaxRows], s_rej[32], s_tie[32];
   __shared__ Decision s_dec;
-  __shared__ double s_pre;
-  __shared__ int s_mm[2 * kAccWaves];
   const int tid = threadIdx.x;
   const int RW = 2 * a.gamma + 1;
-  const int W = gridDim.x;
   const double inv_tau = a.greedy ? 0.0 : 1.0 / a.tau;
-  const unsigned g0 = tid == 0 ? grp_read(gen_word(a)) : 0u;
-  // the inputs of the decisions and the draw for this workgroup's first
-  // batch, loaded up front (drafted position t on thread kAccThreads - 32 + t)
-  const int nd_items = a.greedy ? 1 : a.B * a.ND;
-  const int pb = (int)blockIdx.x < nd_items ? (a.greedy ? 0 : (int)blockIdx.x % a.B) : -1;
+  const int b = (int)blockIdx.x % a.B, c = (int)blockIdx.x / a.B;
+  // the drafted tokens and their logits (position t on thread kAccThreads - 32
+  // + t), loaded up front
   const int t_d = tid - (kAccThreads - 32);
   const bool drafter = t_d >= 0 && t_d < a.gamma;
-  int pf_x = -1;
-  float pf_px = 0.f, pf_qx = 0.f;
-  double pf_ua = 0.0;
-  auto load_draft = [&](int b, int& x, float& px, float& qx, double& ua) {
+  int x = -1;
+  float px = 0.f, qx = 0.f;
+  double ua = 0.0;
+  if (drafter) {
     const int xt = a.tok[(size_t)b * a.gamma + t_d];
     x = xt >= 0 && xt < a.V ? xt : -1;
     if (!a.greedy) {  // clamped loads, all in flight; the values count only when x >= 0
@@ -302,64 +333,13 @@ __global__ void __launch_bounds__(kAccThreads) accept_kernel(AArgs a) {
       qx = row_ptr(a, b, a.gamma + 1 + t_d)[xc];
       ua = a.ua[(size_t)b * a.gamma + t_d];
     }
-  };
-  if (pb >= 0 && drafter) load_draft(pb, pf_x, pf_px, pf_qx, pf_ua);
-  const double pf_us = pb >= 0 && !a.greedy ? a.us[pb] : 0.0;
-
-  // ---- phase 1: chunk max / argmax / exp-sum (greedy: target rows only)
-  const int rows1 = a.greedy ? a.gamma + 1 : RW;
-  const int items1 = a.B * rows1 * a.NC;
-  for (int it = blockIdx.x; it < items1; it += W) {
-    const int c = it % a.NC, rho = (it / a.NC) % rows1, b = it / (a.NC * rows1);
-    const size_t slot = ((size_t)b * RW + rho) * a.NC + c;
-    const float* z = row_ptr(a, b, rho);
-    const int y0 = c * kChunk, y1 = min(a.V, y0 + kChunk);
-    float v[kAccPer];
-    load_strided<VEC>(z, y0, y1, v);
-    float mx = -INFINITY;
-    int am = 0x7fffffff;
-#pragma unroll
-    for (int j = 0; j < kAccPer; ++j)
-      if (v[j] > mx) {  // ascending index order within the thread: first max kept
-        mx = v[j];
-        am = strided_index(y0, j);
-      }
-    block_argmax(mx, am, s_fv, s_fi);
-    double sum = 0.0;
-    if (!a.greedy && mx != -INFINITY) {
-      // no branches around the exponentials (entries past the chunk are -inf
-      // and contribute exp(-inf) = 0), so their evaluations interleave
-      const double M = mx;
-      double e[kAccPer];
-#pragma unroll
-      for (int j = 0; j < kAccPer; ++j) e[j] = exp(((double)v[j] - M) * inv_tau);
-#pragma unroll
-      for (int j = 0; j < kAccPer; ++j) sum += e[j];
-    }
-    sum = block_sum(sum, s_d);
-    if (tid == 0) {
-      st_agent(a.pm + slot, mx == -INFINITY ? kNegInfD : (double)mx);
-      st_agent(a.ps + slot, sum);
-      st_agent(a.pi + slot, am);
-    }
   }
-  const int items3 = a.B * a.ND;
-  const bool draws = !a.greedy && (int)blockIdx.x < items3;
-  const bool greedy_out = a.greedy && blockIdx.x == 0;
-  grid_wait(a, 0, g0, draws || greedy_out);
-
-  // every row's max, argmax and normaliser of batch b, the accept test of
-  // every drafted position (in parallel), and the first rejection, into
+  // every row's max, argmax and normaliser of the batch row, the accept test
+  // of every drafted position (in parallel), and the first rejection, into
   // s_dec (greedy: the outputs)
-  auto decide = [&](int b) {
+  {
     const int rows = a.greedy ? a.gamma + 1 : RW;
-    // the drafted tokens and their logits (threads of the last wave), loaded
-    // up front for the first batch
     const int t = t_d;
-    int x = pf_x;
-    float px = pf_px, qx = pf_qx;
-    double ua = pf_ua;
-    if (drafter && b != pb) load_draft(b, x, px, qx, ua);
     // row r's NC chunk results are combined by an aligned group of NCp lanes
     // (NCp = NC rounded up to a power of two, at most 64), lane k taking
     // chunks k, k + NCp, ...; max and lowest argmax, then the normaliser, by
@@ -375,17 +355,17 @@ __global__ void __launch_bounds__(kAccThreads) accept_kernel(AArgs a) {
       if (act) {
         // the lane's first chunk: its three results loaded together (clamped)
         const int kc = min(k0, a.NC - 1);
-        const double m2 = ld_agent(a.pm + base + kc);
-        const int i2 = ld_agent(a.pi + base + kc);
-        const double sv = a.greedy ? 0.0 : ld_agent(a.ps + base + kc);
+        const double m2 = a.pm[base + kc];
+        const int i2 = a.pi[base + kc];
+        const double sv = a.greedy ? 0.0 : a.ps[base + kc];
         if (k0 < a.NC) {
           m0 = M = m2;
           s0 = sv;
           A = i2;
         }
         for (int k = k0 + NCp; k < a.NC; k += NCp) {
-          const double m3 = ld_agent(a.pm + base + k);
-          const int i3 = ld_agent(a.pi + base + k);
+          const double m3 = a.pm[base + k];
+          const int i3 = a.pi[base + k];
           if (m3 > M || (m3 == M && i3 < A)) {
             M = m3;
             A = i3;
@@ -403,8 +383,8 @@ __global__ void __launch_bounds__(kAccThreads) accept_kernel(AArgs a) {
       double Z = 0.0;
       if (act && !a.greedy && M != kNegInfD)
         for (int k = k0; k < a.NC; k += NCp) {
-          const double m2 = k == k0 ? m0 : ld_agent(a.pm + base + k);
-          const double s2 = k == k0 ? s0 : ld_agent(a.ps + base + k);
+          const double m2 = k == k0 ? m0 : a.pm[base + k];
+          const double s2 = k == k0 ? s0 : a.ps[base + k];
           if (m2 != kNegInfD) Z += s2 * exp((m2 - M) * inv_tau);
         }
       for (int o = NCp / 2; o > 0; o >>= 1) Z += __shfl_xor(Z, o, 64);
@@ -458,180 +438,128 @@ __global__ void __launch_bounds__(kAccThreads) accept_kernel(AArgs a) {
       }
     }
     __syncthreads();
-  };
-
-  if (greedy_out)
-    for (int b = 0; b < a.B; ++b) decide(b);
-  if (a.greedy) return;
-
-  // Entries y = c * kDrawChunk + kDrawPer * tid + j of draw chunk c: r(y) of
-  // the draw distribution (the residual max(0, p - q), or p for the bonus)
-  // or, with want_p, p(y); returns this thread's sum of p(y) as well.
-  auto draw_values = [&](int b, int c, bool want_p, double (&r)[kDrawPer]) -> double {
-    const Decision d = s_dec;
-    const bool resid = !want_p && d.acc < a.gamma;
-    const double ipz = 1.0 / d.pZ, iqz = 1.0 / d.qZ;
-    const float* zpr = row_ptr(a, b, d.acc);
-    const float* zqr = row_ptr(a, b, a.gamma + 1 + min(d.acc, a.gamma - 1));
-    const int y = c * kDrawChunk + kDrawPer * tid;
-    float zp[kDrawPer], zq[kDrawPer];
-#pragma unroll
-    for (int j = 0; j < kDrawPer; ++j) {
-      // clamped loads, all in flight together; past V: p = 0, q = 0
-      const float xp = zpr[min(y + j, a.V - 1)], xq = zqr[min(y + j, a.V - 1)];
-      zp[j] = y + j < a.V ? xp : -INFINITY;
-      zq[j] = y + j < a.V && resid ? xq : -INFINITY;
-    }
-    double psum = 0.0;
-#pragma unroll
-    for (int j = 0; j < kDrawPer; ++j) {
-      const double p = exp(((double)zp[j] - d.pM) * inv_tau) * ipz;
-      const double q = exp(((double)zq[j] - d.qM) * inv_tau) * iqz;
-      psum += p;
-      r[j] = !resid ? p : (p > q ? p - q : 0.0);
-    }
-    return psum;
-  };
-
-  // ---- phase 2: masses of the draw chunks (the values of the workgroup's
-  //      last item are kept)
-  double rr[kDrawPer];
-  double rr_excl = 0.0;  // exclusive prefix of the kept values' thread sums (residual)
-  int kept = -1, dec_b = -1;
-  for (int it = blockIdx.x; it < items3; it += W) {
-    const int b = it % a.B, c = it / a.B;
-    if (b != dec_b) {
-      decide(b);
-      dec_b = b;
-    }
-    const double sp = draw_values(b, c, false, rr);
-    kept = it;
-    double sr = 0.0;
-#pragma unroll
-    for (int j = 0; j < kDrawPer; ++j) sr += rr[j];
-    double tr, tp, ep;
-    block_scan2_f64(sr, sp, s_d, rr_excl, ep, tr, tp);
-    if (tid == 0) {
-      st_agent(a.rs + (size_t)b * a.ND + c, tr);
-      st_agent(a.qs + (size_t)b * a.ND + c, tp);
-    }
   }
-  grid_wait(a, 1, g0, draws);
-  if (!draws) return;
+  if (a.greedy) return;
+  double rr[kDrawPer];
+  const double sp = draw_values<kDrawPer>(a, s_dec, b, c, false, rr);
+  double sr = 0.0;
+#pragma unroll
+  for (int j = 0; j < kDrawPer; ++j) sr += rr[j];
+  double er, ep, tr, tp;
+  block_scan2_f64(sr, sp, s_d, er, ep, tr, tp);
+  if (tid == 0) {
+    a.rs[(size_t)b * a.ND + c] = tr;
+    a.qs[(size_t)b * a.ND + c] = tp;
+    if (c == 0) a.dec[b] = s_dec;
+  }
+}
 
-  // ---- phase 3: the chunk where the cumulative mass first exceeds u' * Z
-  //      scans its values and writes the outputs
-  for (int it = blockIdx.x; it < items3; it += W) {
-    const int b = it % a.B, c = it / a.B;
-    // chunk sums of batch b in order: thread t owns chunks kSumPer * t + i
-    double cr[kSumPer], cq[kSumPer];
-    double own_r = 0.0, own_q = 0.0;
+template <int kDrawPer>
+__global__ void __launch_bounds__(kAccThreads) accept_pick_kernel(AArgs a) {
+  constexpr int kDrawChunk = kAccThreads * kDrawPer;
+  __shared__ double s_d[2 * kAccWaves];
+  __shared__ double s_pre;
+  __shared__ int s_mm[2 * kAccWaves];
+  const int tid = threadIdx.x, b = blockIdx.x;
+  const Decision d = a.dec[b];
+  const double us = a.us[b];
+  // chunk sums of batch b in order: thread t owns chunks kSumPer * t + i
+  double cr[kSumPer], cq[kSumPer];
+  double own_r = 0.0, own_q = 0.0;
 #pragma unroll
-    for (int i = 0; i < kSumPer; ++i) {
-      const int k = kSumPer * tid + i;
-      const double xr = ld_agent(a.rs + (size_t)b * a.ND + min(k, a.ND - 1));  // clamped loads
-      const double xq = ld_agent(a.qs + (size_t)b * a.ND + min(k, a.ND - 1));
-      cr[i] = k < a.ND ? xr : 0.0;
-      cq[i] = k < a.ND ? xq : 0.0;
-      own_r += cr[i];
-      own_q += cq[i];
-    }
-    double Zr, Zq, ex_r, ex_q;
-    block_scan2_f64(own_r, own_q, s_d, ex_r, ex_q, Zr, Zq);
-    const bool use_r = Zr > 0.0;  // else the residual is empty: draw from p
-    const double Z = use_r ? Zr : Zq;
-    const double thr = (b == pb ? pf_us : a.us[b]) * Z;
-    // the first chunk whose cumulative mass passes u' * Z, and the last
-    // chunk with positive mass
-    double run = use_r ? ex_r : ex_q;
-    double pre_of[kSumPer];
-    int first = 0x7fffffff, last = -1;
+  for (int i = 0; i < kSumPer; ++i) {
+    const int k = kSumPer * tid + i;
+    const double xr = a.rs[(size_t)b * a.ND + min(k, a.ND - 1)];  // clamped loads
+    const double xq = a.qs[(size_t)b * a.ND + min(k, a.ND - 1)];
+    cr[i] = k < a.ND ? xr : 0.0;
+    cq[i] = k < a.ND ? xq : 0.0;
+    own_r += cr[i];
+    own_q += cq[i];
+  }
+  double Zr, Zq, ex_r, ex_q;
+  block_scan2_f64(own_r, own_q, s_d, ex_r, ex_q, Zr, Zq);
+  const bool use_r = Zr > 0.0;  // else the residual is empty: draw from p
+  const double Z = use_r ? Zr : Zq;
+  const double thr = us * Z;
+  // the first chunk whose cumulative mass passes u' * Z, and the last
+  // chunk with positive mass
+  double run = use_r ? ex_r : ex_q;
+  double pre_of[kSumPer];
+  int first = 0x7fffffff, last = -1;
 #pragma unroll
-    for (int i = 0; i < kSumPer; ++i) {
-      const int k = kSumPer * tid + i;
-      const double sk = use_r ? cr[i] : cq[i];
-      pre_of[i] = run;
-      if (k < a.ND) {
-        if (first == 0x7fffffff && run + sk > thr) first = k;
-        if (sk > 0.0) last = k;
-      }
-      run += sk;
+  for (int i = 0; i < kSumPer; ++i) {
+    const int k = kSumPer * tid + i;
+    const double sk = use_r ? cr[i] : cq[i];
+    pre_of[i] = run;
+    if (k < a.ND) {
+      if (first == 0x7fffffff && run + sk > thr) first = k;
+      if (sk > 0.0) last = k;
     }
-    block_minmax(first, last, s_mm);
-    const bool fallback = first == 0x7fffffff;  // rounding: no chunk passes u' * Z
-    const int cross = fallback ? max(last, 0) : first;
+    run += sk;
+  }
+  block_minmax(first, last, s_mm);
+  const bool fallback = first == 0x7fffffff;  // rounding: no chunk passes u' * Z
+  const int cross = fallback ? max(last, 0) : first;
 #pragma unroll
-    for (int i = 0; i < kSumPer; ++i)
-      if (kSumPer * tid + i == cross) s_pre = last < 0 ? 0.0 : pre_of[i];
-    __syncthreads();
-    const double pre = s_pre;
-    __syncthreads();
-    if (cross != c) continue;  // uniform across the workgroup
-    if (b != dec_b) {
-      decide(b);
-      dec_b = b;
-    }
-    // the kept values, unless they belong to another item or the draw
-    // falls back to p
-    double excl = rr_excl;
-    if (it != kept || !use_r) {
-      draw_values(b, c, !use_r, rr);
-      kept = use_r ? it : -1;
-      double own = 0.0;
+  for (int i = 0; i < kSumPer; ++i)
+    if (kSumPer * tid + i == cross) s_pre = last < 0 ? 0.0 : pre_of[i];
+  __syncthreads();
+  const double pre = s_pre;
+  __syncthreads();
+  // that chunk's values (p where the residual is empty)
+  double rr[kDrawPer];
+  draw_values<kDrawPer>(a, d, b, cross, !use_r, rr);
+  double own = 0.0;
 #pragma unroll
-      for (int j = 0; j < kDrawPer; ++j) own += rr[j];
-      double tot;
-      excl = block_scan_f64(own, s_d, &tot);
-    }
-    // this thread's first entry passing u' * Z and last positive entry; the
-    // workgroup's first crossing wins, else (rounding, or the fallback
-    // chunk) its last positive entry
-    const int ybase = c * kDrawChunk + kDrawPer * tid;
-    double cum = pre + excl;
-    int cross_y = 0x7fffffff, last_y = -1;
-    double below = cum, at = cum;
+  for (int j = 0; j < kDrawPer; ++j) own += rr[j];
+  double tot;
+  const double excl = block_scan_f64(own, s_d, &tot);
+  // this thread's first entry passing u' * Z and last positive entry; the
+  // workgroup's first crossing wins, else (rounding, or the fallback
+  // chunk) its last positive entry
+  const int ybase = cross * kDrawChunk + kDrawPer * tid;
+  double cum = pre + excl;
+  int cross_y = 0x7fffffff, last_y = -1;
+  double below = cum, at = cum;
 #pragma unroll
-    for (int j = 0; j < kDrawPer; ++j) {
-      const double prev = cum;
-      cum += rr[j];
-      if (!fallback && cross_y == 0x7fffffff && cum > thr) {
-        cross_y = ybase + j;
-        below = prev;
-        at = cum;
-      }
-      if (rr[j] > 0.0) last_y = ybase + j;
+  for (int j = 0; j < kDrawPer; ++j) {
+    const double prev = cum;
+    cum += rr[j];
+    if (!fallback && cross_y == 0x7fffffff && cum > thr) {
+      cross_y = ybase + j;
+      below = prev;
+      at = cum;
     }
-    int lo = cross_y, hi = last_y;
-    block_minmax(lo, hi, s_mm);
-    const bool edge = fallback || lo == 0x7fffffff;
-    const int win = edge ? hi : lo;
-    const int mine = edge ? last_y : cross_y;
-    const Decision d = s_dec;
-    if (win < 0 && tid == 0) {  // no positive mass anywhere: degenerate input
-      dev_flag(a.status, PVLM_DEV_RANGE);
-      a.nacc[b] = d.acc;
-      a.next[b] = 0;
-      if (a.near) a.near[b] = 1;
+    if (rr[j] > 0.0) last_y = ybase + j;
+  }
+  int lo = cross_y, hi = last_y;
+  block_minmax(lo, hi, s_mm);
+  const bool edge = fallback || lo == 0x7fffffff;
+  const int win = edge ? hi : lo;
+  const int mine = edge ? last_y : cross_y;
+  if (win < 0 && tid == 0) {  // no positive mass anywhere: degenerate input
+    dev_flag(a.status, PVLM_DEV_RANGE);
+    a.nacc[b] = d.acc;
+    a.next[b] = 0;
+    if (a.near) a.near[b] = 1;
+  }
+  if (mine == win && win >= 0) {
+    int tie = d.tie;
+    if (!edge) {
+      if (fabs(at - thr) <= kNearTie * Z) tie = 1;
+      if (win > 0 && fabs(below - thr) <= kNearTie * Z) tie = 1;
+    } else {
+      tie = 1;
     }
-    if (mine == win && win >= 0) {
-      int tie = d.tie;
-      if (!edge) {
-        if (fabs(at - thr) <= kNearTie * Z) tie = 1;
-        if (win > 0 && fabs(below - thr) <= kNearTie * Z) tie = 1;
-      } else {
-        tie = 1;
-      }
-      a.nacc[b] = d.acc;
-      a.next[b] = win;
-      if (a.near) a.near[b] = tie;
-    }
-    __syncthreads();
+    a.nacc[b] = d.acc;
+    a.next[b] = win;
+    if (a.near) a.near[b] = tie;
   }
 }
 
 struct APlan {
   int NC, ND;
-  size_t off_arrive, off_gen, off_pm, off_ps, off_pi, off_rs, off_qs, bytes;
+  size_t off_pm, off_ps, off_pi, off_rs, off_qs, bytes;
 };
 
 pvlm_status plan_accept(int B, int gamma, int V, APlan* p) {
@@ -642,9 +570,9 @@ pvlm_status plan_accept(int B, int gamma, int V, APlan* p) {
   p->ND = (V + kAccThreads * kDrawPerMin - 1) / (kAccThreads * kDrawPerMin);  // at most
   const size_t rows = (size_t)B * (2 * gamma + 1);
   const size_t parts = rows * p->NC;
-  // counters inside the fixed synchronisation region, data after it
-  p->off_arrive = 0;
-  p->off_gen = kSyncAcceptOff;
+  // the decisions inside the fixed synchronisation region (written before they
+  // are read in every call), data after it
+  static_assert(kAccMaxB * sizeof(Decision) <= kSyncRegion - kSyncAcceptOff, "decisions fit");
   size_t off = kSyncRegion;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -704,8 +632,7 @@ extern "C" pvlm_status pvlm_spec_accept(int B, int gamma, int V, float temperatu
   a.pi = reinterpret_cast<int*>(wsb + p.off_pi);
   a.rs = reinterpret_cast<double*>(wsb + p.off_rs);
   a.qs = reinterpret_cast<double*>(wsb + p.off_qs);
-  a.arrive = reinterpret_cast<int*>(wsb + p.off_arrive);
-  a.gen = reinterpret_cast<unsigned*>(wsb + p.off_gen);
+  a.dec = reinterpret_cast<Decision*>(wsb + kSyncAcceptOff);
   a.B = B;
   a.gamma = gamma;
   a.V = V;
@@ -715,25 +642,17 @@ extern "C" pvlm_status pvlm_spec_accept(int B, int gamma, int V, float temperatu
   a.ND = (V + kAccThreads * dp - 1) / (kAccThreads * dp);
   a.tau = (double)temperature;
   a.greedy = temperature == 0.f;
-  const int items = max(B * (a.greedy ? gamma + 1 : 2 * gamma + 1) * p.NC, a.greedy ? 1 : B * a.ND);
-  // a multiple of 8 workgroups (the XCD count) keeps the cooperative queue's
-  // round-robin XCD placement aligned for the launches that follow
-  int grid = (items + 7) / 8 * 8;
-  if (grid > di.cus) grid = di.cus;
-  if (grid < 1) grid = 1;
   // float4 loads when every row starts on a 16-byte boundary
   const bool vec = V % 4 == 0 && reinterpret_cast<uintptr_t>(draft_logits) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(target_logits) % 16 == 0;
   void* args[] = {&a};
-  const void* kern =
-      vec ? (dp == kDrawPerMin ? reinterpret_cast<const void*>(accept_kernel<true, kDrawPerMin>)
-                               : reinterpret_cast<const void*>(accept_kernel<true, kDrawPerMax>))
-          : (dp == kDrawPerMin ? reinterpret_cast<const void*>(accept_kernel<false, kDrawPerMin>)
-                               : reinterpret_cast<const void*>(accept_kernel<false, kDrawPerMax>));
-  {
-    const pvlm_status cs = check_coresident(kern, grid, kAccThreads, 0, stream);
-    if (cs != PVLM_OK) return cs;
-  }
-  PVLM_HIP(launch_coresident(kern, dim3(grid), dim3(kAccThreads), args, 0, stream));
+  const auto launch = [&](void (*k)(AArgs), int grid) {
+    return hipLaunchKernel(reinterpret_cast<const void*>(k), dim3(grid), dim3(kAccThreads), args, 0, stream);
+  };
+  PVLM_HIP(launch(vec ? accept_stats_kernel<true> : accept_stats_kernel<false>,
+                  B * (a.greedy ? gamma + 1 : 2 * gamma + 1) * p.NC));
+  const bool few = dp == kDrawPerMin;
+  PVLM_HIP(launch(few ? accept_mass_kernel<kDrawPerMin> : accept_mass_kernel<kDrawPerMax>, a.greedy ? B : B * a.ND));
+  if (!a.greedy) PVLM_HIP(launch(few ? accept_pick_kernel<kDrawPerMin> : accept_pick_kernel<kDrawPerMax>, B));
   return PVLM_OK;
 }
