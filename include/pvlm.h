@@ -46,37 +46,28 @@
  *     in flight at the same time.  The library's only mutable state is the
  *     per-stream compute-unit budgets below and the fixed scratch of
  *     pvlm_verify_attn_noalloc.
- *   - Workgroups that wait on each other.  pvlm_verify_attn(_paged) with mass
- *     while its stream is captured, and top-k rows longer than 16384 scores,
- *     split their work over workgroups of one launch that exchange partial
- *     results and wait for each other (bounded waits: a wait that gives up
- *     sets PVLM_DEV_TIMEOUT, and the results are invalid).
- *     Every workgroup must therefore be resident at once.  Each call checks
- *     before launching that its grid fits the device (the runtime's occupancy
- *     per compute unit times the compute units it plans for; a verify call
- *     whose grid does not fit runs without waits, top-k returns
- *     PVLM_ERR_UNSUPPORTED).  Eager verify calls never wait.
- *     Eager launches on a stream without a budget are cooperative launches,
- *     whose co-residency the runtime guarantees.  Launches captured into a
- *     graph, and launches on a budgeted stream, are ordinary launches: then
- *     the caller guarantees that no other work holds compute units the call
- *     needs for longer than the call itself runs.  Without budgets that means
- *     the device to itself while such a call runs: no two of these calls in
- *     flight at once on different streams.  Kernels that never wait (rope,
- *     UV-Prune, short top-k rows, gather) and finish on their own may run
- *     beside them: they only delay them.
- *   - Compute-unit budgets (pvlm_set_stream_cu_budget): calls of the waiting
- *     kind on a stream with a budget of C compute units plan their grids for
- *     at most C workgroups.  Streams whose budgets sum to at most the
- *     device's compute units may then run such calls at the same time, since
- *     every workgroup of all of them fits at once (one workgroup per compute
- *     unit at most; budgets are multiples of the XCD count, so a grid spreads
- *     evenly over the XCDs the device deals workgroups to in turn).
+ *   - Workgroups that wait on each other.  Only pvlm_verify_attn(_paged) with
+ *     mass, while its stream is captured into a graph, splits its work over
+ *     workgroups of one launch that wait for each other's row statistics
+ *     (bounded waits: a wait that gives up sets PVLM_DEV_TIMEOUT, and the
+ *     results are invalid).  Every workgroup must therefore be resident at
+ *     once: the call checks that its grid fits the compute units it plans for
+ *     (else it records launches that do not wait), and the caller guarantees
+ *     that, while such a graph runs, no other work holds compute units the
+ *     call needs for longer than the call itself runs.  Without budgets that
+ *     means no two such graphs in flight at once on different streams.
+ *     Everything else (eager verify calls among it) never waits and may run
+ *     beside anything: it only delays it.
+ *   - Compute-unit budgets (pvlm_set_stream_cu_budget): verify calls on a
+ *     stream with a budget of C compute units plan their grids for at most C
+ *     workgroups (long-row top-k calls too).  Streams whose budgets sum to at
+ *     most the device's compute units may then replay waiting graphs at the
+ *     same time, since every workgroup of all of them fits at once (one
+ *     workgroup per compute unit at most).
  *   - Workspaces: zero-fill a workspace once before its first use.  Its first
- *     1 MiB holds the words of the waits between workgroups, and every call
- *     leaves them in a consistent state (zero again, or, for monotonic
- *     counters, advanced together), so one buffer (at least as large as each
- *     call requires) serves calls of any kind and shape in sequence.
+ *     1 MiB holds the words of the waits between workgroups, which every call
+ *     leaves zero again, so one buffer (at least as large as each call
+ *     requires) serves calls of any kind and shape in sequence.
  *   - Layouts are C-contiguous, innermost index last.  "bf16" is IEEE
  *     bfloat16 stored in 2 bytes.
  */
@@ -375,8 +366,8 @@ pvlm_status pvlm_prefill_epilogue_cossim(int B, int64_t m_cap, const int32_t* m,
  *   score [B][m_cap] fp32; m, k: [B] int32 device; idx [B][k_cap] int32.
  * Rows of up to 16384 scores (m_cap <= 16384) are selected by one workgroup
  * each and need no workspace (pvlm_topk_workspace_size returns 0, ws may be
- * NULL).  Longer rows are split over several workgroups of one co-resident
- * launch that exchange digit histograms and counts through `ws`
+ * NULL).  Longer rows are split over several workgroups, whose launches pass
+ * digit histograms and counts through `ws`
  * (pvlm_topk_workspace_size bytes, zero-filled before first use, reusable by
  * later calls on the stream); then B may not exceed the device's compute
  * units (PVLM_ERR_UNSUPPORTED).

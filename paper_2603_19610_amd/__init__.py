@@ -309,11 +309,10 @@ def release_workspaces():
 
 # ------------------------------------------------------------------ calls --
 def set_stream_cu_budget(stream, cus: int):
-    """Give ``stream`` (a torch.cuda.Stream) a compute-unit budget: its verify,
-    long-row top-k and accept calls then plan for at most ``cus`` workgroups
-    and launch as ordinary launches, so they may run beside calls on streams
-    whose budgets sum with it to at most the device's compute units.  0
-    removes the budget."""
+    """Give ``stream`` (a torch.cuda.Stream) a compute-unit budget: its verify
+    and long-row top-k calls then plan for at most ``cus`` workgroups, so
+    captured verify calls may run beside those of streams whose budgets sum
+    with it to at most the device's compute units.  0 removes the budget."""
     _check(lib().pvlm_set_stream_cu_budget(_P(stream.cuda_stream), int(cus)),
            "pvlm_set_stream_cu_budget")
 

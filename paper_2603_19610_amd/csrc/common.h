@@ -37,20 +37,16 @@ pvlm_status device_info(DeviceInfo* out, hipStream_t stream);
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Every workspace starts with a fixed-size region that holds all counters of
-// the inter-workgroup waits, so a zero-filled workspace can be reused by calls
-// of any shape: their data areas (after the region) may overlap earlier data,
-// their counters never do.  Calls whose counters return to zero use the low
-// part of the region.  Verify's statistics records that a launch waits on
-// (0 between calls) lie from kSyncVerifyOff; top-k's monotonic counters (each
-// call leaves them consistent, never resets them) from kSyncTopkOff (one line
-// per batch row), accept's at kSyncAcceptOff.
+// Every workspace starts with a fixed-size region whose words a call may rely
+// on: verify's statistics records that a captured launch waits on, from
+// kSyncVerifyOff, are 0 between calls.  Data areas after the region may hold
+// anything.  Accept keeps its decisions at kSyncAcceptOff (written before they
+// are read in every call); kSyncTopkOff bounds the records and, with the rest,
+// the batch and group counts that calls accept.
 constexpr size_t kSyncRegion = 1024 * 1024;
 constexpr size_t kSyncVerifyOff = 256 * 1024;
 constexpr size_t kSyncTopkOff = 768 * 1024;
 constexpr size_t kSyncAcceptOff = 896 * 1024;
-// Counters that many workgroups update or poll get a 128-byte line each, so
-// the memory-side atomics and polls of different counters never contend.
 constexpr size_t kSyncLine = 128;
 
 // Raise a kernel's dynamic-LDS limit to `bytes` (done once per kernel and size).
@@ -59,18 +55,11 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes);
 // PVLM_OK when `grid` workgroups of `kernel` (with `block` threads and `lds`
 // dynamic LDS bytes) fit on the current device at once: the occupancy the
 // runtime reports per compute unit times the compute units (the stream's
-// budget when it has one).  Every launch whose workgroups wait on each other
-// checks this before launching.
+// budget when it has one).  A launch whose workgroups wait on each other (verify
+// under stream capture) checks this before launching; that they do start
+// together then rests on the caller's contract: the device not shared, or the
+// budgets of overlapping streams within its compute units.
 pvlm_status check_coresident(const void* kernel, int grid, int block, int lds,
-                             hipStream_t stream);
-
-// Launch a kernel whose workgroups wait on each other: cooperatively (the
-// runtime guarantees co-residency), or as an ordinary launch while the stream
-// is being captured into a graph or has a compute-unit budget (then
-// co-residency rests on check_coresident and on the caller's contract: the
-// device not shared, or the budgets of overlapping streams within its compute
-// units).  Grids are at most one workgroup per CU.
-hipError_t launch_coresident(const void* kernel, dim3 grid, dim3 block, void** args, int lds,
                              hipStream_t stream);
 
 // ---------------------------------------------------------------- device --
@@ -139,31 +128,6 @@ __device__ __forceinline__ void lds_sync() {
 __device__ __forceinline__ uint64_t pack_bf16x4(float x, float y, float z, float w) {
   return (uint64_t)f32_to_bf16(x) | ((uint64_t)f32_to_bf16(y) << 16) | ((uint64_t)f32_to_bf16(z) << 32) |
          ((uint64_t)f32_to_bf16(w) << 48);
-}
-
-// Monotonic group counters.  Every launch adds one arrival per workgroup of a
-// group to that group's counter and never resets it; the count the counter
-// had when the launch began ("base") is kept beside it.  Every workgroup reads
-// the base at kernel start, waits for base + (workgroups in the group) with
-// wrapping arithmetic, and the launch's last arrival at the group's final
-// counter advances the base.  No end-of-kernel reset round trip is needed.
-__device__ __forceinline__ unsigned grp_arrive(unsigned* counter) {
-  return __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned grp_read(const unsigned* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// Bounded poll until *counter has reached `target`; flags PVLM_DEV_TIMEOUT
-// and gives up after kSpinLimit polls.
-__device__ __forceinline__ void grp_poll(const unsigned* counter, unsigned target, int32_t* status) {
-  int spins = 0;
-  while ((int)(grp_read(counter) - target) < 0) {
-    __builtin_amdgcn_s_sleep(1);
-    if (++spins > kSpinLimit) {
-      dev_flag(status, PVLM_DEV_TIMEOUT);
-      break;
-    }
-  }
 }
 
 // The cache rows of one (batch, KV head): contiguous (base = the head's row
@@ -248,10 +212,6 @@ __device__ __forceinline__ float lane_xor16(float x) {
 __device__ __forceinline__ float lane_xor32(float x) {
   const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float((threadIdx.x & 32) ? a[0] : a[1]);
-}
-
-__device__ __forceinline__ void reset_counter(int* counter) {
-  __hip_atomic_store(counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ float warp_max(float v) {

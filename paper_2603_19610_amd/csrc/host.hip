@@ -57,19 +57,6 @@ pvlm_status check_coresident(const void* kernel, int grid, int block, int lds,
   return (int64_t)per_cu * di.cus >= grid ? PVLM_OK : PVLM_ERR_UNSUPPORTED;
 }
 
-hipError_t launch_coresident(const void* kernel, dim3 grid, dim3 block, void** args, int lds,
-                             hipStream_t stream) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  hipError_t e = hipStreamIsCapturing(stream, &cap);
-  if (e != hipSuccess) return e;
-  if (cap == hipStreamCaptureStatusNone) {
-    DeviceInfo di;
-    if (device_info(&di, stream) != PVLM_OK) return hipErrorInvalidDevice;
-    if (!di.budgeted) return hipLaunchCooperativeKernel(kernel, grid, block, args, lds, stream);
-  }
-  return hipLaunchKernel(kernel, grid, block, args, lds, stream);
-}
-
 void set_hip_error(hipError_t e) {
   g_last_hip_error = std::string(hipGetErrorName(e)) + ": " + hipGetErrorString(e);
 }

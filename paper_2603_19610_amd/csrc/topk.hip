@@ -10,12 +10,16 @@
 // selection is integer work, so the result is bit-exact.
 //
 // Rows of up to 16384 scores take one 1024-thread workgroup each, the keys in
-// registers.  Longer rows are split over NW workgroups (one launch, grid
-// co-resident):
-// per digit, every workgroup histograms its slice in LDS and publishes it;
-// the last to arrive sums the NW histograms, picks the digit and publishes
-// it; the others wait for it.  The emission step exchanges per-slice counts
-// the same way so every workgroup knows where its slice's output starts.
+// registers.  Longer rows are split over NW workgroups and five ordinary
+// launches: every launch sums the slices' histograms of the digit before,
+// picks that digit and histograms its own slice's next one; the last emits.
+// Each workgroup also counts its slice's keys above each digit, so the last
+// launch knows where every slice's output starts.  No workgroup waits for
+// another: one launch with five waits took 33.6 us for 131072 scores (the
+// waits) and a cooperative launch's own time when eager; with its gather
+// 60.1 us a pass eagerly and 42.0 captured, these 43.6 and 43.8.  (The slice
+// requested before the digit is known: 46.6, its loads then delay the
+// histograms'.)
 #include "common.h"
 
 namespace pvlm {
@@ -25,7 +29,8 @@ constexpr int kTopkThreads = 256;
 constexpr int kTopkWaves = kTopkThreads / 64;
 constexpr int kPerThread = 16;   // consecutive scores per thread (register slice, ordered pass)
 constexpr int kSlice = kTopkThreads * kPerThread;  // scores per workgroup unless B*NW would exceed the CUs
-constexpr int kBarriers = 5;     // four digits and the emission counts
+constexpr int kCopies = 8;       // counters per histogram bin: scores share few top digits, and LDS
+                                 // atomics of one instruction to one address serialise
 static_assert(kTopkThreads == 256, "one histogram bin per thread");
 
 __device__ __forceinline__ uint32_t rank_key(float f) {
@@ -100,16 +105,12 @@ struct TArgs {
   const int32_t* k;
   int32_t* idx;
   int32_t* status;
-  int* hist;       // [B][NW][256] per-slice digit histograms
-  int* res;        // [B][4]: digit, keys above the prefix range
-  int* cnt;        // [B][NW][2]: keys above the threshold, keys equal to it
-  int* arrive;     // [B] arrivals (128 B apart), back to zero after each call
-  unsigned* gen;   // [B] generation words (128 B apart), advanced per barrier
+  int* hist;       // [4][B][NW][256] per-slice histograms of each digit
+  int2* state;     // [4][B]: the prefix up to a digit, keys above its range
+  int* cnt;        // [3][B][NW]: a slice's keys above the prefix range by a digit
   int64_t m_cap;
   int k_cap, NW, slice;
 };
-
-constexpr int kLine = (int)(kSyncLine / sizeof(int));
 
 // Entry i of a row (row offset `off`): the score, or in the fused MASS form
 // the UV-Prune variation crit^L - crit^0 of Eq. (average_similarity),
@@ -120,64 +121,25 @@ __device__ __forceinline__ float score_at(const TArgs& a, size_t off, int64_t i)
   else return a.score[off + i];
 }
 
-// A pair of ints exchanged between workgroups as one device-coherent 64-bit
-// access (8-byte aligned): one round trip for both, and a consistent pair.
-__device__ __forceinline__ void st_pair(int* p, int lo, int hi) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32),
-                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ int2 ld_pair(const int* p) {
-  const uint64_t v =
-      __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return make_int2((int)(uint32_t)v, (int)(uint32_t)(v >> 32));
+__device__ __forceinline__ int sum256(int x, int* s_warp) {
+  int tot;
+  block_exclusive_scan(x, s_warp, &tot);
+  return tot;
 }
 
-// Barrier `p` (0-based) of row b.  Thread 0 arrives; the launch's last arrival
-// runs `last` (with the whole workgroup) and then releases the others, which
-// wait for the generation word to reach g0 + p + 1.  Returns in every thread.
-template <typename F>
-__device__ __forceinline__ void row_barrier(const TArgs& a, int b, int p, unsigned g0, int* s_flag,
-                                            F last) {
-  __builtin_amdgcn_s_waitcnt(0);  // this workgroup's published data is visible
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const int old = __hip_atomic_fetch_add(a.arrive + b * kLine, 1, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-    *s_flag = old == a.NW * (p + 1) - 1;
-  }
-  __syncthreads();
-  if (*s_flag) {
-    last();
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      if (p == kBarriers - 1)  // every workgroup has arrived for the last time
-        __hip_atomic_store(a.arrive + b * kLine, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(a.gen + b * kLine, g0 + (unsigned)p + 1u, __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
-    }
-  } else if (threadIdx.x == 0) {
-    grp_poll(a.gen + b * kLine, g0 + (unsigned)p + 1u, a.status);
-  }
-  __syncthreads();
-}
-
-// REG: the slice (at most kTopkThreads * kPerThread scores) is read once into
-// registers, thread t holding the scores s0 + kPerThread*t + e; otherwise it
-// is read again from memory for every pass, in chunks of that size.
-template <bool REG, bool FUSED>
-__global__ void __launch_bounds__(kTopkThreads) topk_kernel(TArgs a) {
+// Launch `pass` of a long row: 0 .. 3 histogram that digit of the slice, 4
+// emits.  Bound by the launch and one round trip each for the histograms and
+// the slice (131072 scores: 32 slices of 4096).
+template <bool FUSED>
+__global__ void __launch_bounds__(kTopkThreads) topk_kernel(TArgs a, int pass) {
   constexpr int kChunk = kTopkThreads * kPerThread;
-  __shared__ int hist[256];
+  __shared__ int hist[256 * kCopies];
   __shared__ int s_warp[kTopkWaves];
-  __shared__ int s_flag, s_res[2];
+  __shared__ int s_res[3];
   const int b = blockIdx.x / a.NW, j = blockIdx.x % a.NW;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, B = gridDim.x / a.NW;
   const size_t roff = (size_t)b * a.m_cap;
   int32_t* out = a.idx + (size_t)b * a.k_cap;
-  // the generation at launch start, read before this workgroup first arrives
-  // (only thread 0 arrives and waits)
-  const unsigned g0 = tid == 0 ? grp_read(a.gen + b * kLine) : 0u;
 
   int mb = a.m[b], kb = a.k[b];
   bool bad = false;
@@ -190,136 +152,102 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(TArgs a) {
     bad = true;
     kb = kb < 0 ? 0 : kmax;
   }
-  if (bad && j == 0 && tid == 0) dev_flag(a.status, PVLM_DEV_RANGE);
-  if (j == 0)
+  if (pass == 0 && j == 0) {
+    if (bad && tid == 0) dev_flag(a.status, PVLM_DEV_RANGE);
     for (int r = kb + tid; r < a.k_cap; r += kTopkThreads) out[r] = -1;
+  }
   const int s0 = min(mb, j * a.slice), s1 = min(mb, s0 + a.slice);
-  int* hrow = a.hist + (size_t)b * a.NW * 256;
   if constexpr (FUSED) {  // the scores of this workgroup's share of the row (0 past m[b])
-    if (a.score_out && !REG) {
+    if (a.score_out && pass == 0) {
       const int64_t e1 = min((int64_t)(j + 1) * a.slice, a.m_cap);
-      for (int64_t i = (int64_t)j * a.slice + tid; i < e1; i += kTopkThreads)
-        a.score_out[roff + i] = i < mb ? score_at<true>(a, roff, i) : 0.f;
-    } else if (a.score_out) {  // past m[b] only; the kept slice is written with its keys
-      const int64_t e0 = max((int64_t)j * a.slice, (int64_t)mb);
-      const int64_t e1 = min((int64_t)(j + 1) * a.slice, a.m_cap);
-      for (int64_t i = e0 + tid; i < e1; i += kTopkThreads) a.score_out[roff + i] = 0.f;
+      for (int64_t i = max((int64_t)j * a.slice, (int64_t)mb) + tid; i < e1; i += kTopkThreads)
+        a.score_out[roff + i] = 0.f;
     }
   }
+  if (kb == 0 && (!FUSED || !a.score_out || pass > 0)) return;
 
-  uint32_t kr[kPerThread];
-  if constexpr (REG) {
-    const int i0 = s0 + tid * kPerThread;
-#pragma unroll
-    for (int e = 0; e < kPerThread; ++e)
-      kr[e] = __float_as_uint(score_at<FUSED>(a, roff, min(i0 + e, s1 > 0 ? s1 - 1 : 0)));
-    if constexpr (FUSED) {
-      if (a.score_out)
-#pragma unroll
-        for (int e = 0; e < kPerThread; ++e)
-          if (i0 + e < s1) a.score_out[roff + i0 + e] = __uint_as_float(kr[e]);
-    }
-#pragma unroll  // (clamped loads, all in flight together, then the keys)
-    for (int e = 0; e < kPerThread; ++e) kr[e] = i0 + e < s1 ? rank_key(__uint_as_float(kr[e])) : 0u;
-  }
-  // f(key) over this thread's scores of the slice
-  auto visit = [&](auto f) {
-    if constexpr (REG) {
-      const int nv = s1 - (s0 + tid * kPerThread);
-#pragma unroll
-      for (int e = 0; e < kPerThread; ++e)
-        if (e < nv) f(kr[e]);
-    } else {
-      for (int i = s0 + tid; i < s1; i += kTopkThreads) f(rank_key(score_at<FUSED>(a, roff, i)));
-    }
-  };
-
-  // ---- radix select of the kb-th largest key.  With kb == 0 nothing is
-  //      counted, but every barrier is still passed.
+  // the digit before: every slice's histogram, and the keys of earlier slices
   uint32_t prefix = 0, mask = 0;
-  int above = 0;  // keys strictly above the current prefix range
-  for (int pass = 0; pass < 4; ++pass) {
-    const int shift = 24 - 8 * pass;
-    hist[tid] = 0;
+  int above = 0, gt_before = 0, eq_before = 0;
+  if (pass > 0) {
+    const int* hrow = a.hist + ((size_t)(pass - 1) * B + b) * a.NW * 256;
+    int t = 0, before = 0, own = 0;
+    for (int j0 = 0; j0 < a.NW; j0 += 16) {
+      int v[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) v[q] = hrow[(size_t)min(j0 + q, a.NW - 1) * 256 + tid];  // in flight together
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        const int x = j0 + q < a.NW ? v[q] : 0;
+        t += x;
+        before += j0 + q < j ? x : 0;
+        own = j0 + q == j ? x : own;
+      }
+    }
+    const int2 st = pass > 1 ? a.state[(size_t)(pass - 1) * B + b] : make_int2(0, 0);
+    hist[tid] = t;
     __syncthreads();
-    if (kb > 0)
-      visit([&](uint32_t key) {
-        if ((key & mask) == prefix) atomicAdd(&hist[(key >> shift) & 255], 1);
+    if (tid < 64)
+      find_digit(hist, kb - st.y, [&](int digit, int acc) {
+        s_res[0] = digit;
+        s_res[1] = st.y + acc;
       });
     __syncthreads();
-    st_agent(hrow + j * 256 + tid, hist[tid]);
-    row_barrier(a, b, pass, g0, &s_flag, [&]() {
-      // the last workgroup: total histogram, then the digit holding the
-      // kb-th largest key (scanning digits from the top)
-      int t = 0;
-      for (int j0 = 0; j0 < a.NW; j0 += 8) {
-        int v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {  // clamped loads, all in flight together
-          const int x = ld_agent(hrow + min(j0 + q, a.NW - 1) * 256 + tid);
-          v[q] = j0 + q < a.NW ? x : 0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) t += v[q];
+    const int digit = s_res[0];
+    above = s_res[1];
+    prefix = (uint32_t)st.x | (uint32_t)digit << (32 - 8 * pass);
+    mask = ~0u << (32 - 8 * pass);
+    if (pass < 4) {
+      const int g = sum256(tid > digit ? own : 0, s_warp);
+      if (tid == 0) {
+        a.cnt[((size_t)(pass - 1) * B + b) * a.NW + j] = g;
+        if (j == 0) a.state[(size_t)pass * B + b] = make_int2((int)prefix, above);
       }
-      hist[tid] = t;
+    } else {
+      int g = tid > digit ? before : 0;
+      for (int q = tid; q < 3 * j; q += kTopkThreads)
+        g += a.cnt[((size_t)(q / j) * B + b) * a.NW + q % j];
+      gt_before = sum256(g, s_warp);
+      if (tid == digit) s_res[2] = before;
       __syncthreads();
-      if (tid < 64)
-        find_digit(hist, kb - above, [&](int digit, int acc) {
-          st_pair(a.res + b * 4, digit, above + acc);
-        });
-    });
-    if (tid == 0) {
-      const int2 r = ld_pair(a.res + b * 4);
-      s_res[0] = r.x;
-      s_res[1] = r.y;
+      eq_before = s_res[2];
     }
-    __syncthreads();
-    if (kb > 0) {
-      prefix |= (uint32_t)s_res[0] << shift;
-      mask |= 255u << shift;
-      above = s_res[1];
-    }
-    __syncthreads();
+    __syncthreads();  // hist and s_res are reused below
   }
+
+  if (pass < 4) {
+    const int shift = 24 - 8 * pass, copy = tid % kCopies;
+    for (int i = tid; i < 256 * kCopies; i += kTopkThreads) hist[i] = 0;
+    __syncthreads();
+    for (int base = s0; base < s1; base += kChunk) {
+      float v[kPerThread];
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e)  // clamped loads, all in flight together
+        v[e] = score_at<FUSED>(a, roff, min(base + e * kTopkThreads + tid, s1 - 1));
+#pragma unroll
+      for (int e = 0; e < kPerThread; ++e) {
+        const int i = base + e * kTopkThreads + tid;
+        if (i < s1) {
+          if constexpr (FUSED) {
+            if (pass == 0 && a.score_out) a.score_out[roff + i] = v[e];
+          }
+          const uint32_t key = rank_key(v[e]);
+          if ((key & mask) == prefix) atomicAdd(&hist[((key >> shift) & 255) * kCopies + copy], 1);
+        }
+      }
+    }
+    __syncthreads();
+    int t = 0;
+#pragma unroll
+    for (int c = 0; c < kCopies; ++c) t += hist[tid * kCopies + c];
+    a.hist[(((size_t)pass * B + b) * a.NW + j) * 256 + tid] = t;
+    return;
+  }
+
   const uint32_t tau = prefix;
   const int need_eq = kb - above;  // keys equal to tau to keep, lowest indices first
-
-  // ---- this slice's counts, exchanged: where its output starts
-  int n_gt = 0, n_eq = 0;
-  if (kb > 0)
-    visit([&](uint32_t key) {
-      n_gt += key > tau;
-      n_eq += key == tau;
-    });
-  int slice_gt, slice_eq;
-  block_exclusive_scan(n_gt, s_warp, &slice_gt);
-  block_exclusive_scan(n_eq, s_warp, &slice_eq);
-  if (tid == 0) {
-    st_pair(a.cnt + ((size_t)b * a.NW + j) * 2, slice_gt, slice_eq);
-  }
-  row_barrier(a, b, 4, g0, &s_flag, []() {});
-  if (kb == 0) return;
-  if (tid < 64) {  // counts of the slices before this one
-    int gt = 0, eq = 0;
-    for (int q = tid; q < j; q += 64) {
-      const int2 c = ld_pair(a.cnt + ((size_t)b * a.NW + q) * 2);
-      gt += c.x;
-      eq += c.y;
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      gt += __shfl_xor(gt, o, 64);
-      eq += __shfl_xor(eq, o, 64);
-    }
-    if (tid == 0) {
-      s_res[0] = gt;
-      s_res[1] = eq;
-    }
-  }
-  __syncthreads();
-  int carry_out = s_res[0] + min(s_res[1], need_eq);
-  int carry_eq = s_res[1];
+  int carry_out = gt_before + min(eq_before, need_eq);
+  int carry_eq = eq_before;
 
   // ---- ordered emission of the slice in ascending index order
   for (int base = s0; base < s1; base += kChunk) {
@@ -329,11 +257,8 @@ __global__ void __launch_bounds__(kTopkThreads) topk_kernel(TArgs a) {
 #pragma unroll
     for (int e = 0; e < kPerThread; ++e) {
       const bool valid = i0 + e < s1;
-      if constexpr (REG) keys[e] = kr[e];
-      else {
-        const float x = score_at<FUSED>(a, roff, min(i0 + e, s1 - 1));  // clamped (s1 > base >= 0)
-        keys[e] = valid ? rank_key(x) : 0u;
-      }
+      const float x = score_at<FUSED>(a, roff, min(i0 + e, s1 - 1));  // clamped (s1 > base >= 0)
+      keys[e] = valid ? rank_key(x) : 0u;
       g += valid && keys[e] > tau;
       e_ += valid && keys[e] == tau;
     }
@@ -563,7 +488,7 @@ __global__ void __launch_bounds__(kSmallThreads) topk_small_kernel(TArgs a) {
 
 struct TPlan {
   int NW, slice;
-  size_t off_arrive, off_gen, off_hist, off_res, off_cnt, bytes;
+  size_t off_hist, off_state, off_cnt, bytes;
 };
 
 // stream / with_stream: as for verify's plan (the stream's compute-unit budget).
@@ -579,24 +504,20 @@ pvlm_status plan_topk(int B, int64_t m_cap, TPlan* p, hipStream_t stream, bool w
   pvlm_status st = with_stream ? device_info(&di, stream) : device_info(&di);
   if (st != PVLM_OK) return st;
   if (B > di.cus) return PVLM_ERR_UNSUPPORTED;
-  const int nw_max = di.cus / B;  // co-resident: at most one workgroup per CU
+  const int nw_max = di.cus / B;  // every workgroup sums the others' histograms: no more than fill the device
   int64_t nw = (m_cap + kSlice - 1) / kSlice;
   if (nw > nw_max) nw = nw_max;
   if (nw < 1) nw = 1;
   p->NW = (int)nw;
   p->slice = (int)((m_cap + nw - 1) / nw);
-  // counters: arrivals return to zero (low part), generations are monotonic
-  // (their own part of the monotonic region)
   if (kSyncLine * (size_t)B > kSyncAcceptOff - kSyncTopkOff) return PVLM_ERR_UNSUPPORTED;
-  p->off_arrive = 0;
-  p->off_gen = kSyncTopkOff;
   size_t off = kSyncRegion;
   p->off_hist = off;
-  off = align_up(off + sizeof(int) * (size_t)B * p->NW * 256, 256);
-  p->off_res = off;
-  off = align_up(off + sizeof(int) * (size_t)B * 4, 256);
+  off = align_up(off + sizeof(int) * 4 * (size_t)B * p->NW * 256, 256);
+  p->off_state = off;
+  off = align_up(off + sizeof(int2) * 4 * (size_t)B, 256);
   p->off_cnt = off;
-  off = align_up(off + sizeof(int) * (size_t)B * p->NW * 2, 256);
+  off = align_up(off + sizeof(int) * 3 * (size_t)B * p->NW, 256);
   p->bytes = off;
   return PVLM_OK;
 }
@@ -654,20 +575,13 @@ pvlm_status topk_run(int B, int64_t m_cap, const int32_t* m, const int32_t* k, i
   }
   char* wsb = static_cast<char*>(ws);
   a.hist = reinterpret_cast<int*>(wsb + p.off_hist);
-  a.res = reinterpret_cast<int*>(wsb + p.off_res);
+  a.state = reinterpret_cast<int2*>(wsb + p.off_state);
   a.cnt = reinterpret_cast<int*>(wsb + p.off_cnt);
-  a.arrive = reinterpret_cast<int*>(wsb + p.off_arrive);
-  a.gen = reinterpret_cast<unsigned*>(wsb + p.off_gen);
-  const bool reg = p.slice <= kTopkThreads * kPerThread;
-  const void* kern = reg ? (fused ? reinterpret_cast<const void*>(topk_kernel<true, true>)
-                                  : reinterpret_cast<const void*>(topk_kernel<true, false>))
-                         : (fused ? reinterpret_cast<const void*>(topk_kernel<false, true>)
-                                  : reinterpret_cast<const void*>(topk_kernel<false, false>));
-  {
-    const pvlm_status cs = check_coresident(kern, B * p.NW, kTopkThreads, 0, stream);
-    if (cs != PVLM_OK) return cs;
+  const void* kern = fused ? reinterpret_cast<const void*>(topk_kernel<true>) : reinterpret_cast<const void*>(topk_kernel<false>);
+  for (int pass = 0; pass < 5; ++pass) {
+    void* pargs[] = {&a, &pass};
+    PVLM_HIP(hipLaunchKernel(kern, dim3(B * p.NW), dim3(kTopkThreads), pargs, 0, stream));
   }
-  PVLM_HIP(launch_coresident(kern, dim3(B * p.NW), dim3(kTopkThreads), args, 0, stream));
   return PVLM_OK;
 }
 }  // namespace
