@@ -790,6 +790,7 @@ __attribute__((amdgpu_waves_per_eu(PartShape<M, RT>::kWpe, PartShape<M, RT>::kWp
 template <typename M, typename PT>
 __device__ void combine_row(const VArgs& a, int64_t id) {
   constexpr int D = M::D, PC = 16 / sizeof(PT), LPR = D / PC, SG = 64 / LPR, kU = 8;
+  static_assert(64 % (kU * SG) == 0, "a batch of chunks shares one weight register");
   if (id >= (int64_t)a.B * a.Hkv * a.R) return;
   const int lane = threadIdx.x & 63, sg = lane / LPR, col = lane % LPR;
   const int bg = (int)(id / a.R), row = (int)(id - (int64_t)bg * a.R);
@@ -804,33 +805,54 @@ __device__ void combine_row(const VArgs& a, int64_t id) {
   uint4 v[kU];
 #pragma unroll
   for (int j = 0; j < kU; ++j) v[j] = op[min(sg + j * SG, nsp - 1) * os];
+  // the statistics of 256 chunks at a time, all in flight together: few rows
+  // over many chunks are bound by this wave's round trips (63K tokens, 18
+  // rows, 247 chunks, us a layer with the rotary append: 24.1 with 64 at a
+  // time and a second read, 22.0 this way)
+  constexpr int kC = 4;
+  float2 x[kC];
+  auto load_stats = [&](int s0) {
+#pragma unroll
+    for (int c = 0; c < kC; ++c)
+      if (c == 0 || s0 + 64 * c < nsp) x[c] = st[(size_t)min(s0 + 64 * c + lane, nsp - 1) * 16];
+#pragma unroll
+    for (int c = 0; c < kC; ++c)
+      if (s0 + 64 * c + lane >= nsp) x[c] = make_float2(kNegInf, 0.f);
+  };
   float Mx = kNegInf, Z = 0.f;
-  for (int s0 = 0; s0 < nsp; s0 += 64) {
-    const float2 x = st[(size_t)min(s0 + lane, nsp - 1) * 16];
-    const float m = s0 + lane < nsp ? x.x : kNegInf;
+  for (int s0 = 0; s0 < nsp; s0 += 64 * kC) {
+    load_stats(s0);
+    float m = x[0].x;
+#pragma unroll
+    for (int c = 1; c < kC; ++c) m = fmaxf(m, x[c].x);
     const float bm = warp_max(m);
-    const float e = m == kNegInf ? 0.f : fast_exp2(m - bm);
-    lse_combine(Mx, Z, bm, warp_sum(s0 + lane < nsp ? x.y * e : 0.f));
+    float e = 0.f;
+#pragma unroll
+    for (int c = 0; c < kC; ++c) e += x[c].x == kNegInf ? 0.f : x[c].y * fast_exp2(x[c].x - bm);
+    lse_combine(Mx, Z, bm, warp_sum(e));
   }
   const bool ok = Z > 0.f;
   const float inv = ok ? 1.f / Z : 0.f;
   float acc[PC];
 #pragma unroll
   for (int c = 0; c < PC; ++c) acc[c] = 0.f;
-  for (int s0 = 0; s0 < nsp; s0 += 64) {
-    const float2 x = st[(size_t)min(s0 + lane, nsp - 1) * 16];
-    const float wt = s0 + lane < nsp && x.x != kNegInf ? fast_exp2(x.x - Mx) * inv : 0.f;
-    const int cnt = min(64, nsp - s0);
-    for (int k0 = 0; k0 < cnt; k0 += kU * SG) {
+  for (int s0 = 0; s0 < nsp; s0 += 64 * kC) {
+    if (nsp > 64 * kC) load_stats(s0);
+    float wt[kC];
+#pragma unroll
+    for (int c = 0; c < kC; ++c) wt[c] = x[c].x == kNegInf ? 0.f : fast_exp2(x[c].x - Mx) * inv;
+    const int cnt = min(64 * kC, nsp - s0);
+    for (int k0 = 0; k0 < cnt; k0 += kU * SG) {  // kU * SG divides 64
       if (s0 + k0 > 0) {
 #pragma unroll
         for (int j = 0; j < kU; ++j) v[j] = op[min(s0 + k0 + sg + j * SG, nsp - 1) * os];
       }
+      const int kc = k0 / 64;  // uniform
+      const float w = kc == 0 ? wt[0] : kc == 1 ? wt[1] : kc == 2 ? wt[2] : wt[3];
 #pragma unroll
       for (int j = 0; j < kU; ++j) {
         const int s = k0 + sg + j * SG;
-        const float f0 = __shfl(wt, s & 63, 64);
-        const float f = s < cnt ? f0 : 0.f;
+        const float f = __shfl(w, s & 63, 64);
         float p[PC];
         unpack(v[j], p);
 #pragma unroll
