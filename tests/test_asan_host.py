@@ -31,7 +31,8 @@ def _sources():
 
 def _digest():
     h = hashlib.sha256()
-    for p in _sources() + [DRIVER, os.path.join(CSRC, "common.h"), os.path.join(ROOT, "include", "pvlm.h")]:
+    headers = sorted(os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h"))
+    for p in _sources() + headers + [DRIVER, os.path.join(ROOT, "include", "pvlm.h")]:
         h.update(open(p, "rb").read())
     return h.hexdigest()
 
