@@ -324,7 +324,9 @@ __device__ __forceinline__ const typename M::E* q_row(const VArgs& a, int b, int
 // the chunk fetch its last row again (their probabilities are 0).  The loads
 // are inline asm, so the compiler neither counts them nor waits for them: the
 // loading wave, which issues no other vector memory operation in its loop,
-// counts them itself (wait_stage).
+// counts them itself (wait_stage).  Nor does it look for hazards inside the
+// asm: an LDS load may not directly follow the scalar write of M0 that gives
+// its LDS address (one wait state), hence the s_nop.
 template <typename M, bool SWIZZLE>
 __device__ __forceinline__ void issue_block(const KvRows& kv, int tb, int c1, char* lds, int lane) {
   constexpr int D = M::D, CH = M::CH, RPI = 64 / CH, NI = M::BLK / RPI;
@@ -336,7 +338,7 @@ __device__ __forceinline__ void issue_block(const KvRows& kv, int tb, int c1, ch
     const typename M::E* src = r0 + (size_t)(min(tb + row, c1 - 1) - te) * D +
                                (16 / sizeof(typename M::E)) * (SWIZZLE ? c ^ (row % CH) : c);
     const uint32_t at = __builtin_amdgcn_readfirstlane(lds_addr(lds + k * 1024));
-    asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "memory", "m0");
   }
 }
 // Wait until at most `stages` later stages' loads (N per stage) are in flight.
