@@ -36,12 +36,13 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes);
 
 // PVLM_OK when `grid` workgroups of `kernel` (with `block` threads and `lds`
 // dynamic LDS bytes) fit on the current device at once: the occupancy the
-// runtime reports per compute unit times the compute units (the stream's
-// budget when it has one).  A launch whose workgroups wait on each other (verify
+// runtime reports per compute unit, but at most `per_cu_most` (the runtime does
+// not count registers that a waves-per-SIMD bound reserves beyond those used),
+// times the compute units (the stream's budget when it has one).  A launch whose workgroups wait on each other (verify
 // under stream capture) checks this before launching; that they do start
 // together then rests on the caller's contract: the device not shared, or the
 // budgets of overlapping streams within its compute units.
-pvlm_status check_coresident(const void* kernel, int grid, int block, int lds,
+pvlm_status check_coresident(const void* kernel, int grid, int block, int lds, int per_cu_most,
                              hipStream_t stream);
 
 // ---------------------------------------------------------------- device --

@@ -33,7 +33,7 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes) {
   return e;
 }
 
-pvlm_status check_coresident(const void* kernel, int grid, int block, int lds,
+pvlm_status check_coresident(const void* kernel, int grid, int block, int lds, int per_cu_most,
                              hipStream_t stream) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
@@ -54,6 +54,7 @@ pvlm_status check_coresident(const void* kernel, int grid, int block, int lds,
   DeviceInfo di;
   const pvlm_status st = device_info(&di, stream);
   if (st != PVLM_OK) return st;
+  if (per_cu > per_cu_most) per_cu = per_cu_most;
   return (int64_t)per_cu * di.cus >= grid ? PVLM_OK : PVLM_ERR_UNSUPPORTED;
 }
 

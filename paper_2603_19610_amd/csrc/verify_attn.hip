@@ -433,7 +433,7 @@ struct PartShape {
   static constexpr int kThreads = (RT * TW + kLoaders) * 64;
   static constexpr int kHalf = ST * M::D * (int)sizeof(typename M::E);  // bytes of a stage's K (or V)
   static constexpr int kLds = kSlots * 2 * kHalf;
-  static constexpr int kWpe = (RT * TW + kLoaders + 3) / 4;  // one workgroup per CU
+  static constexpr int kWpe = (kPerCu * (RT * TW + kLoaders) + 3) / 4;  // waves per SIMD
 };
 
 template <typename M, int RT, int RES>
@@ -1072,7 +1072,7 @@ pvlm_status verify_run(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int6
   if (mass && p.fused && cap != hipStreamCaptureStatusNone && 128 * records <= (int64_t)(kSyncTopkOff - kSyncVerifyOff)) {
     const void* k = reinterpret_cast<const void*>(p.fused);
     PVLM_HIP(allow_dynamic_lds(k, p.lds));
-    if (check_coresident(k, (int)grid.x, p.threads, p.lds, stream) == PVLM_OK) {
+    if (check_coresident(k, (int)grid.x, p.threads, p.lds, kPerCu, stream) == PVLM_OK) {
       a.clear = true;
       a.stats = reinterpret_cast<float2*>(wsb + kSyncVerifyOff);
       PVLM_HIP(hipLaunchKernel(k, grid, block, args, p.lds, stream));

@@ -12,10 +12,17 @@
 namespace pvlm {
 
 constexpr int kMaxRT = 9;  // 16-row tiles per workgroup of the partial kernel
+// Workgroups of the partial and mass kernels that a compute unit holds, at
+// either head dim: their waves-per-SIMD bound makes them reserve a unit's
+// registers (two tiles reserve 176 of a lane's 512 for each of six waves), and
+// at D = 128 their ring takes its LDS.  The runtime's occupancy figure counts
+// the registers they use, so a launch that waits has to go by this one.
+constexpr int kPerCu = 1;
 
 struct VSplit {
   int G, R, RTT, RG, RT;
   int splits, chunk;
+  int slots;  // workgroups of the partial kernel that run at once
   bool o32;
   size_t off_stats, off_opart, off_mpart, bytes;
 };
@@ -84,10 +91,10 @@ inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   const int blk = bf16 ? 32 : 16, e = bf16 ? 2 : 4;
   const int64_t tiles = (int64_t)B * Hkv * p->RTT;
   // chunks of whole stages (two blocks)
-  const int64_t nst = (n_plan + 2 * blk - 1) / (2 * blk), slots = (int64_t)di.cus * (D == 128 || di.budgeted ? 1 : 2);
-  // One workgroup per compute unit (its ring takes most of the LDS; two at
-  // D = 64, where no budget has to be kept), all of them in one round, and at
-  // least two stages each: fewer would only add partials.
+  const int64_t nst = (n_plan + 2 * blk - 1) / (2 * blk), slots = (int64_t)di.cus * kPerCu;
+  p->slots = (int)slots;
+  // One workgroup per compute unit, all of them in one round, and at least two
+  // stages each: fewer would only add partials.
   auto chunk_stages = [&](int64_t groups) {
     const int64_t cs = (nst * groups + slots - 1) / slots;
     return cs < 2 ? (int64_t)2 : cs;

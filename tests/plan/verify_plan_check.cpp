@@ -1,0 +1,65 @@
+// Runs verify attention's plan over its sizes without a GPU.
+//   verify_plan_check resident WG   no plan counts on more than WG workgroups
+//                                   of a compute unit at once
+// Prints the first failures and their number.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+
+#include "verify_plan.h"
+
+using namespace pvlm;
+
+struct Call {
+  pvlm_dtype dt;
+  int B, T, Hq, Hkv, D;
+  int64_t n_cap, ctx;
+};
+
+template <typename F>
+static void each_call(F f) {
+  const int64_t ctxs[] = {0,    1,    62,   63,   64,    127,   333,   787,   1300,  1919,  4096,   6432,
+                          8192, 9000, 12800, 14300, 14400, 16384, 20000, 32768, 63000, 70000, 131072, 500000};
+  for (int dt = 0; dt < 2; ++dt)
+    for (int D : {64, 128})
+      for (int Hkv : {1, 2, 3, 4, 5, 7, 8, 12, 16})
+        for (int G : {1, 4, 5, 7, 8, 16, 32})
+          for (int T : {1, 2, 4, 6, 9, 12, 17, 32})
+            for (int B : {1, 2, 3, 4, 5, 6, 7, 8, 40})
+              for (int64_t ctx : ctxs) {
+                const Call c{dt ? PVLM_BF16 : PVLM_F32, B, T, G * Hkv, Hkv, D, ctx + T + (ctx % 3) * 50, ctx};
+                if (check_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx) == PVLM_OK) f(c);
+              }
+}
+
+template <typename F>
+static long failures(F bad) {
+  long n = 0, fail = 0;
+  DeviceInfo whole;
+  whole.cus = 256;
+  whole.xcds = 8;
+  each_call([&](const Call& c) {
+    for (int cus : {256, 248, 224, 128, 104, 40, 32, 8}) {
+      DeviceInfo di = whole;
+      di.cus = cus;
+      di.budgeted = cus != whole.cus;
+      VSplit p;
+      if (split_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx, di, &p) != PVLM_OK) continue;
+      ++n;
+      if (bad(c, di, p) && fail++ < 10)
+        std::printf("%s B %d T %d heads %d/%d D %d ctx %lld on %d: %d x %d tiles, %d chunks of %d, slots %d\n",
+                    c.dt == PVLM_BF16 ? "bf16" : "fp32", c.B, c.T, c.Hq, c.Hkv, c.D, (long long)c.ctx, cus, p.RG,
+                    p.RT, p.splits, p.chunk, p.slots);
+    }
+  });
+  std::printf("%ld of %ld plans fail\n", fail, n);
+  return n == 0 ? 1 : fail;
+}
+
+int main(int argc, char** argv) {
+  if (argc == 3 && !std::strcmp(argv[1], "resident")) {
+    const int wg = std::atoi(argv[2]);
+    return failures([&](const Call&, const DeviceInfo& di, const VSplit& p) { return p.slots > wg * di.cus; }) != 0;
+  }
+  return 2;
+}

@@ -69,6 +69,10 @@ def _check(inp, got, hq, T):
     (1, 32, 20, 1, 128, [333], "bf16"),            # 640 rows: 40 tiles
     (3, 5, 7, 1, 128, [5000, 0, 257], "bf16"),     # padding rows, empty chunks
     (1, 1, 8, 8, 128, [20000], "bf16"),            # one tile, ten stages resident
+    (1, 2, 32, 8, 64, [4096], "bf16"),             # D = 64: one workgroup a compute unit, resident
+    (1, 4, 32, 8, 64, [8192], "bf16"),
+    (1, 4, 32, 8, 64, [2100], "f32"),
+    (40, 2, 32, 8, 64, [300] * 40, "bf16"),        # 320 workgroups: more than fit, so two passes
     (1, 5, 4, 1, 64, [31], "f32"),                 # fp32 stages of 32 rows
     (1, 5, 4, 1, 64, [1024], "f32"),
     (2, 7, 14, 2, 128, [95, 31], "f32"),           # four fp32 tiles
