@@ -93,16 +93,17 @@ inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   // chunks of whole stages (two blocks)
   const int64_t nst = (n_plan + 2 * blk - 1) / (2 * blk), slots = (int64_t)di.cus * kPerCu;
   p->slots = (int)slots;
-  // One workgroup per compute unit, all of them in one round, and at least two
-  // stages each: fewer would only add partials.
+  // One workgroup per compute unit, all of them in one round (as many chunks as
+  // every group has compute units for: one workgroup more would run alone in a
+  // second round), and at least two stages each: fewer would only add partials.
   auto chunk_stages = [&](int64_t groups) {
-    const int64_t cs = (nst * groups + slots - 1) / slots;
+    const int64_t most = slots > groups ? slots / groups : 1, cs = (nst + most - 1) / most;
     return cs < 2 ? (int64_t)2 : cs;
   };
   const int64_t heads = (int64_t)B * Hkv;
   const size_t per_split = (size_t)tiles * 16 * (8 + (size_t)D * e);
   const int rg6 = (p->RTT + 5) / 6;
-  if (p->RT > 6 && nst * heads * rg6 <= 7 * slots) {
+  if (p->RT > 6 && heads * rg6 <= slots && chunk_stages(heads * rg6) <= 7) {
     // Seven row tiles or more leave a wave 168 registers: no room for resident
     // scores.  Chunks that stay within seven stages with up to six tiles go to
     // more workgroups (K and V read again, from L2); longer ones would pay for

@@ -1,6 +1,10 @@
 // Runs verify attention's plan over its sizes without a GPU.
 //   verify_plan_check resident WG   no plan counts on more than WG workgroups
 //                                   of a compute unit at once
+//   verify_plan_check round         a plan's workgroups run in one round
+//                                   wherever its groups of row tiles do
+//   verify_plan_check areas         the areas follow each other inside the
+//                                   workspace, every cache row in one chunk
 // Prints the first failures and their number.
 #include <cstdio>
 #include <cstdlib>
@@ -61,5 +65,20 @@ int main(int argc, char** argv) {
     const int wg = std::atoi(argv[2]);
     return failures([&](const Call&, const DeviceInfo& di, const VSplit& p) { return p.slots > wg * di.cus; }) != 0;
   }
+  if (argc == 2 && !std::strcmp(argv[1], "round"))
+    return failures([&](const Call& c, const DeviceInfo&, const VSplit& p) {
+             const int64_t groups = (int64_t)c.B * c.Hkv * p.RG;
+             return groups * p.splits > p.slots && (groups <= p.slots || p.splits > 1);
+           }) != 0;
+  if (argc == 2 && !std::strcmp(argv[1], "areas"))
+    return failures([&](const Call& c, const DeviceInfo&, const VSplit& p) {
+             const size_t tiles = (size_t)c.B * c.Hkv * p.RTT, e = p.o32 ? 4 : 2;
+             const int64_t n = c.ctx + c.T;
+             return p.RT > kMaxRT || p.RT * p.RG < p.RTT || p.off_mpart < kSyncRegion ||
+                    p.off_stats < p.off_mpart + 4 * (size_t)c.B * c.Hkv * p.RG * c.n_cap ||
+                    p.off_opart < p.off_stats + 128 * tiles * p.splits ||
+                    p.bytes < p.off_opart + tiles * p.splits * 16 * c.D * e ||
+                    (int64_t)p.chunk * p.splits < n || (int64_t)p.chunk * (p.splits - 1) >= n;
+           }) != 0;
   return 2;
 }

@@ -56,3 +56,13 @@ def test_plan_counts_on_resident_workgroups_only(check):
     fit = {k: _resident(*k[1:]) for k in kernels}
     assert min(fit.values()) >= 1, [k for k, v in fit.items() if v < 1]
     check("resident", min(fit.values()))
+
+
+def test_plan_runs_in_one_round(check):
+    """Chunks are as long as it takes for every group's chunks to fit the
+    device together: one workgroup too many doubles the launch's time."""
+    check("round")
+
+
+def test_plan_fits_its_workspace(check):
+    check("areas")
