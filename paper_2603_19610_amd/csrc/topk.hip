@@ -577,9 +577,14 @@ pvlm_status topk_run(int B, int64_t m_cap, const int32_t* m, const int32_t* k, i
   a.hist = reinterpret_cast<int*>(wsb + p.off_hist);
   a.state = reinterpret_cast<int2*>(wsb + p.off_state);
   a.cnt = reinterpret_cast<int*>(wsb + p.off_cnt);
-  const void* kern = fused ? reinterpret_cast<const void*>(topk_kernel<true>) : reinterpret_cast<const void*>(topk_kernel<false>);
   for (int pass = 0; pass < 5; ++pass) {
+    // The fused form writes the scores in its first launch and reads them in
+    // the others: half the bytes of the criteria, which may be gone by then
+    // (the caller may have the scores written over them).
+    const bool crit = fused && (pass == 0 || !score_out);
+    if (fused && !crit) a.score = score_out;
     void* pargs[] = {&a, &pass};
+    const void* kern = crit ? reinterpret_cast<const void*>(topk_kernel<true>) : reinterpret_cast<const void*>(topk_kernel<false>);
     PVLM_HIP(hipLaunchKernel(kern, dim3(B * p.NW), dim3(kTopkThreads), pargs, 0, stream));
   }
   return PVLM_OK;
