@@ -55,9 +55,7 @@ namespace {
 
 constexpr int kLoaders = 2;      // its loading waves: one for K, one for V
 constexpr int kSlots = 4;        // LDS slots of its ring, a stage of K and V rows each
-constexpr int kFinWaves = 4;     // waves of a finish workgroup
-constexpr int kFinThreads = kFinWaves * 64;
-constexpr int kFinTokens = kFinThreads;  // cache rows whose mass one of them sums
+constexpr int kFinWaves = kFinThreads / 64;  // waves of a finish workgroup
 constexpr int kPageSlots = 512;  // page-table entries a workgroup stages in LDS
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -90,6 +88,7 @@ struct VArgs {
   float* mass;
   int32_t* status;
   int mass_wgs, comb_wgs;  // finish kernel: workgroups of each role
+  int64_t mass_pieces;     // ... and pieces of kFinThreads cache rows that the first share out
   bool o32;                // O partials are fp32
   bool clear;              // ... which also clears the statistics
 };
@@ -883,35 +882,34 @@ __device__ void combine_row(const VArgs& a, int64_t id) {
 
 // The mass of every cache row: the sum of its KV heads' and row groups'
 // partials in order (0 past the sequence).
-__device__ __forceinline__ void sum_mass(const VArgs& a, int id) {
+__device__ __forceinline__ void sum_mass(const VArgs& a, int64_t id) {
   constexpr int kP = 8;
   const int P = a.Hkv * a.RG;
-  const int64_t per = (a.n_cap + kFinTokens - 1) / kFinTokens;
+  const int64_t per = (a.n_cap + kFinThreads - 1) / kFinThreads;
   const int b = (int)(id / per);
-  const int64_t t0 = (id - b * per) * kFinTokens;
+  const int64_t t = (id - b * per) * kFinThreads + threadIdx.x;
+  if (t >= a.n_cap) return;
   const int N = seq_ctx(a, b, false) + a.T;
   const float* mp = a.mpart + (size_t)b * P * a.n_cap;
-  float* mass = a.mass + (size_t)b * a.n_cap;
-  for (int64_t t = t0 + threadIdx.x; t < min(t0 + kFinTokens, a.n_cap); t += kFinThreads) {
-    float sum = 0.f;
-    if (t < N)
-      for (int p0 = 0; p0 < P; p0 += kP) {
-        float v[kP];
+  float sum = 0.f;
+  if (t < N)
+    for (int p0 = 0; p0 < P; p0 += kP) {
+      float v[kP];
 #pragma unroll
-        for (int j = 0; j < kP; ++j) v[j] = mp[(size_t)min(p0 + j, P - 1) * a.n_cap + t];
+      for (int j = 0; j < kP; ++j) v[j] = mp[(size_t)min(p0 + j, P - 1) * a.n_cap + t];
 #pragma unroll
-        for (int j = 0; j < kP; ++j)
-          if (p0 + j < P) sum += v[j];
-      }
-    mass[t] = sum;
-  }
+      for (int j = 0; j < kP; ++j)
+        if (p0 + j < P) sum += v[j];
+    }
+  a.mass[(size_t)b * a.n_cap + t] = sum;
 }
 
 template <typename M>
 __global__ void __launch_bounds__(kFinThreads) verify_finish_kernel(VArgs a) {
   const int id = blockIdx.x;
-  if (id < a.mass_wgs) sum_mass(a, id);
-  else if (a.o32) combine_row<M, float>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
+  if (id < a.mass_wgs) {
+    for (int64_t i = id; i < a.mass_pieces; i += a.mass_wgs) sum_mass(a, i);
+  } else if (a.o32) combine_row<M, float>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
   else combine_row<M, typename M::E>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
 }
 
@@ -1059,7 +1057,8 @@ pvlm_status verify_run(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int6
   a.units = B * Hkv * p.RG * p.splits;
   a.sl2 = scale * kLog2e;
   a.o32 = p.o32;
-  a.mass_wgs = mass ? (int)(B * ((n_cap + kFinTokens - 1) / kFinTokens)) : 0;
+  a.mass_wgs = mass ? mass_workgroups(B, n_cap) : 0;
+  a.mass_pieces = mass_pieces(B, n_cap);
   a.comb_wgs = (B * Hkv * p.R + kFinWaves - 1) / kFinWaves;
   // While a stream is captured, a call whose chunks' scores stay in registers
   // is one waiting launch; otherwise the mass is a second pass over K.

@@ -74,6 +74,17 @@ inline pvlm_status check_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   return (int64_t)(Hq / Hkv) * T > 640 ? PVLM_ERR_UNSUPPORTED : PVLM_OK;
 }
 
+// Finish kernel: workgroups that sum the mass, each kFinThreads cache rows at a
+// time.  They take the rest of a long row in turn: with one workgroup for every
+// kFinThreads rows a launch would pass the 2^32 threads that it may hold.
+constexpr int kFinThreads = 256;
+constexpr int64_t kMassWgs = 1 << 16;
+inline int64_t mass_pieces(int B, int64_t n_cap) { return B * ((n_cap + kFinThreads - 1) / kFinThreads); }
+inline int mass_workgroups(int B, int64_t n_cap) {
+  const int64_t n = mass_pieces(B, n_cap);
+  return (int)(n < kMassWgs ? n : kMassWgs);
+}
+
 // The plan on a device (or a stream's budget) of di.cus compute units, for
 // arguments that check_verify takes.
 inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int64_t n_cap,

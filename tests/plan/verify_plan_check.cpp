@@ -5,6 +5,8 @@
 //                                   wherever its groups of row tiles do
 //   verify_plan_check areas         the areas follow each other inside the
 //                                   workspace, every cache row in one chunk
+//   verify_plan_check finish        the finish kernel's grid within a launch's
+//                                   limit, to the longest cache
 // Prints the first failures and their number.
 #include <cstdio>
 #include <cstdlib>
@@ -80,5 +82,16 @@ int main(int argc, char** argv) {
                     p.bytes < p.off_opart + tiles * p.splits * 16 * c.D * e ||
                     (int64_t)p.chunk * p.splits < n || (int64_t)p.chunk * (p.splits - 1) >= n;
            }) != 0;
+  if (argc == 2 && !std::strcmp(argv[1], "finish")) {
+    long fail = 0;
+    for (int B : {1, 3, 4, 64, 2048})
+      for (int64_t n_cap : {(int64_t)1, (int64_t)256, (int64_t)257, (int64_t)1 << 24, ((int64_t)1 << 30) - 1, (int64_t)1 << 30}) {
+        const int64_t wgs = mass_workgroups(B, n_cap), rows = (int64_t)640 * 2048;  // rows of O, four a workgroup
+        fail += wgs < 1 || wgs > mass_pieces(B, n_cap) || (wgs + rows / 4) * kFinThreads >= (int64_t)1 << 32 ||
+                mass_pieces(B, n_cap) * kFinThreads < B * n_cap;
+      }
+    std::printf("%ld grids fail\n", fail);
+    return fail != 0;
+  }
   return 2;
 }

@@ -66,3 +66,7 @@ def test_plan_runs_in_one_round(check):
 
 def test_plan_fits_its_workspace(check):
     check("areas")
+
+
+def test_finish_grid_stays_within_a_launch(check):
+    check("finish")

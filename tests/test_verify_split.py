@@ -108,3 +108,25 @@ def test_unaligned_views(dt):
     got = pv.verify_attn(shift(inp.q), shift(inp.k), shift(inp.v), to_dev(inp.ctx_len), scale=inp.scale)
     torch.cuda.synchronize()
     _check(inp, got, 8, 4)
+
+
+def test_mass_of_a_long_page_table():
+    """More logical cache rows than the finish kernel has workgroups times
+    rows: its workgroups take several pieces each, and the rows past the
+    sequence are 0."""
+    inp = W.random_verify_inputs(1, 3, 4, 1, 64, [100], "bf16", seed=8, n_cap=128)
+    pages = (1 << 24) // 32 + 1000
+    note(f"verify: page table of {pages} pages")
+    q, ctx = to_dev(inp.q), to_dev(inp.ctx_len)
+    k, v = (to_dev(x).view(1, 1, 4, 32, 64).transpose(1, 2).reshape(4, 1, 32, 64).contiguous()
+            for x in (inp.k, inp.v))
+    table = torch.full((1, pages), -1, dtype=torch.int32, device="cuda")
+    table[0, :4] = torch.arange(4, dtype=torch.int32, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    got = pv.verify_attn_paged(q, k, v, table, ctx, scale=inp.scale, max_ctx=100, status=status,
+                               mass=torch.full((1, 32 * pages), 5.0, device="cuda"))
+    ref = pv.verify_attn(q, to_dev(inp.k), to_dev(inp.v), ctx, scale=inp.scale, max_ctx=100, status=status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    assert torch.equal(got[0], ref[0]) and torch.equal(got[2], ref[2])
+    assert torch.equal(got[1][:, :103], ref[1][:, :103]) and not got[1][:, 103:].any()
