@@ -976,16 +976,19 @@ void pick_kernels(VPlan* p) {
 }
 
 // stream: the launch's stream, whose compute-unit budget bounds the plan;
-// with_stream false plans for the whole device (workspace sizes, an upper
-// bound for every budget).
+// with_stream false plans for the whole device (workspace sizes, enough for
+// every budget).
 pvlm_status plan_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int64_t n_cap,
                         int64_t max_ctx, VPlan* p, hipStream_t stream, bool with_stream) {
   pvlm_status st = check_verify(dt, B, T, Hq, Hkv, D, n_cap, max_ctx);
   if (st != PVLM_OK) return st;
-  DeviceInfo di;
-  st = with_stream ? device_info(&di, stream) : device_info(&di);
+  DeviceInfo whole, di;
+  st = device_info(&whole);
   if (st != PVLM_OK) return st;
-  st = split_verify(dt, B, T, Hq, Hkv, D, n_cap, max_ctx, di, p);
+  di = whole;
+  if (with_stream) st = device_info(&di, stream);
+  if (st != PVLM_OK) return st;
+  st = split_verify(dt, B, T, Hq, Hkv, D, n_cap, max_ctx, whole, di, p);
   if (st != PVLM_OK) return st;
   if (dt == PVLM_BF16) {
     if (D == 128) pick_kernels<Bf16<128>>(p);

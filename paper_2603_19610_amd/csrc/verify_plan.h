@@ -27,8 +27,8 @@ struct VSplit {
   size_t off_stats, off_opart, off_mpart, bytes;
 };
 
-// The workspace size that callers are told: a bound that every plan below
-// keeps within, a function of the sizes and the compute units alone, so that
+// The workspace size that callers are told (for the whole device): a bound
+// that every plan below keeps within, a function of the sizes and the compute units alone, so that
 // buffers sized by it and the fixed scratch take the same calls whatever the
 // split.  Per group one statistics record and one fp32-sized partial for
 // each of `splits` chunks, and one mass row per KV head and row group.
@@ -85,10 +85,10 @@ inline int mass_workgroups(int B, int64_t n_cap) {
   return (int)(n < kMassWgs ? n : kMassWgs);
 }
 
-// The plan on a device (or a stream's budget) of di.cus compute units, for
+// The plan on a device, or on a stream's budget `di` of a device `whole`, for
 // arguments that check_verify takes.
-inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int64_t n_cap,
-                                int64_t max_ctx, const DeviceInfo& di, VSplit* p) {
+inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int64_t n_cap, int64_t max_ctx,
+                                const DeviceInfo& whole, const DeviceInfo& di, VSplit* p) {
   p->G = Hq / Hkv;
   p->R = p->G * T;
   const bool bf16 = dt == PVLM_BF16;
@@ -97,6 +97,13 @@ inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   bool ok;
   p->bytes = workspace_bound(bf16, B, Hkv, D, p->RTT, n_cap, n_plan, di, &ok);
   if (!ok) return PVLM_ERR_UNSUPPORTED;
+  if (di.budgeted) {
+    // callers size a workspace for the whole device, whose bound can be the
+    // smaller one (six to nine tiles in chunks that only the budget makes long)
+    bool whole_ok;
+    const size_t sized = workspace_bound(bf16, B, Hkv, D, p->RTT, n_cap, n_plan, whole, &whole_ok);
+    if (whole_ok && sized < p->bytes) p->bytes = sized;
+  }
   p->RG = (p->RTT + kMaxRT - 1) / kMaxRT;
   p->RT = (p->RTT + p->RG - 1) / p->RG;
   const int blk = bf16 ? 32 : 16, e = bf16 ? 2 : 4;

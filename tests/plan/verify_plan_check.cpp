@@ -7,6 +7,8 @@
 //                                   workspace, every cache row in one chunk
 //   verify_plan_check finish        the finish kernel's grid within a launch's
 //                                   limit, to the longest cache
+//   verify_plan_check sized         a workspace sized for the whole device is
+//                                   enough under every budget
 // Prints the first failures and their number.
 #include <cstdio>
 #include <cstdlib>
@@ -50,7 +52,7 @@ static long failures(F bad) {
       di.cus = cus;
       di.budgeted = cus != whole.cus;
       VSplit p;
-      if (split_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx, di, &p) != PVLM_OK) continue;
+      if (split_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx, whole, di, &p) != PVLM_OK) continue;
       ++n;
       if (bad(c, di, p) && fail++ < 10)
         std::printf("%s B %d T %d heads %d/%d D %d ctx %lld on %d: %d x %d tiles, %d chunks of %d, slots %d\n",
@@ -92,6 +94,15 @@ int main(int argc, char** argv) {
       }
     std::printf("%ld grids fail\n", fail);
     return fail != 0;
+  }
+  if (argc == 2 && !std::strcmp(argv[1], "sized")) {
+    DeviceInfo whole;
+    whole.cus = 256;
+    whole.xcds = 8;
+    return failures([&](const Call& c, const DeviceInfo&, const VSplit& p) {
+             VSplit w;
+             return split_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx, whole, whole, &w) == PVLM_OK && p.bytes > w.bytes;
+           }) != 0;
   }
   return 2;
 }

@@ -70,3 +70,9 @@ def test_plan_fits_its_workspace(check):
 
 def test_finish_grid_stays_within_a_launch(check):
     check("finish")
+
+
+def test_workspace_size_holds_under_every_budget(check):
+    """pvlm_verify_attn_workspace_size knows no stream: its answer has to do on
+    streams with any compute-unit budget."""
+    check("sized")

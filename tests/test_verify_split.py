@@ -130,3 +130,22 @@ def test_mass_of_a_long_page_table():
     assert int(status.item()) == 0
     assert torch.equal(got[0], ref[0]) and torch.equal(got[2], ref[2])
     assert torch.equal(got[1][:, :103], ref[1][:, :103]) and not got[1][:, 103:].any()
+
+
+def test_workspace_of_the_queried_size_on_a_budgeted_stream():
+    """Seven and more tiles, and chunks that only the budget makes long: the
+    size asked for without a stream is enough."""
+    inp = W.random_verify_inputs(8, 32, 4, 1, 64, [4096] + [700] * 7, "bf16", seed=12)
+    note("verify: queried workspace on a stream of 128 compute units")
+    s = torch.cuda.Stream()
+    pv.set_stream_cu_budget(s, 128)
+    try:
+        args = [to_dev(x) for x in (inp.q, inp.k, inp.v, inp.ctx_len)]
+        ws = pv.Workspace(torch.device("cuda", 0))
+        torch.cuda.synchronize()
+        with torch.cuda.stream(s):
+            got = pv.verify_attn(*args, scale=inp.scale, max_ctx=4096, ws=ws)
+        torch.cuda.synchronize()
+    finally:
+        pv.set_stream_cu_budget(s, 0)
+    _check(inp, got, 4, 32)
