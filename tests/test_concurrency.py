@@ -1,13 +1,16 @@
 """GPU: the co-residency contract of the calls whose workgroups wait on each
-other (verify attention, long-row top-k, accept).
+other (verify attention with mass, captured into a graph while its chunks'
+scores stay in registers), and calls on several streams at once.
 
-Under graph capture those calls are ordinary launches, and the waits of
-their workgroups rely on every workgroup becoming resident.  Another
-stream's bounded kernels (here GEMMs) can hold compute units for a while;
-the waits then last until those kernels retire.  A replay must then give
-exactly the eager result, or flag PVLM_DEV_TIMEOUT when a wait gave up: never
-a silently wrong result.  Default workspaces are per stream, so calls on two
-streams never share counters."""
+The waits rely on every workgroup becoming resident.  Another stream's bounded
+kernels (here GEMMs) can hold compute units for a while; the waits then last
+until those kernels retire.  A replay must then give exactly the eager result,
+or flag PVLM_DEV_TIMEOUT when a wait gave up: never a silently wrong result.
+Two waiting graphs may run together on streams whose budgets fit the device.
+Default workspaces are per stream, so calls on two streams never share
+records."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -18,6 +21,17 @@ import workloads as W
 from gpu_util import assert_mass, assert_out, f64, note, to_dev, to_host_f64
 
 pytestmark = pytest.mark.gpu
+
+
+def _kernels(graph):
+    """Kernel nodes of a captured graph (CUDAGraph(keep_graph=True))."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    raw, n = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    return n.value
+
+
+WAITING = 2  # launches of the waiting form: the partial kernel, the finish; three where it is two passes
 
 
 def test_captured_verify_beside_busy_stream():
@@ -35,9 +49,11 @@ def test_captured_verify_beside_busy_stream():
     status = torch.zeros(1, dtype=torch.int32, device=dev)
     pv.verify_attn(q, k, v, ctx, out=out, mass=mass, lse=lse, ws=ws, status=status)  # sizes ws
     torch.cuda.synchronize()
-    g = torch.cuda.CUDAGraph()
+    g = torch.cuda.CUDAGraph(keep_graph=True)
     with torch.cuda.graph(g):
         pv.verify_attn(q, k, v, ctx, out=out, mass=mass, lse=lse, ws=ws, status=status)
+    assert _kernels(g) == WAITING
+    g.instantiate()
     torch.cuda.synchronize()
     other = torch.cuda.Stream()
     a = torch.randn((4096, 4096), device=dev, dtype=torch.bfloat16)
@@ -56,7 +72,7 @@ def test_captured_verify_beside_busy_stream():
         st = int(status.item())
         if st & pv.PVLM_DEV_TIMEOUT:
             timeouts += 1
-            ws.buf.zero_()             # counters undefined after a timeout
+            ws.buf.zero_()             # records undefined after a timeout
             torch.cuda.synchronize()
             continue
         assert st == 0, f"device status {st}"
@@ -89,12 +105,12 @@ def test_default_workspaces_are_per_stream():
 
 
 @pytest.mark.parametrize("budgets,first", [((224, 32), "72b"), ((128, 128), "72b"), ((224, 32), "wide")])
-def test_two_budgeted_streams_run_waiting_calls_together(budgets, first):
-    """Verify (72B layer, or 136 rows per KV head over a 20K-token cache, the
-    wide variant) on one budgeted stream and verify + accept (7B layer) on
-    another, enqueued together and repeated: every result equals the same
-    call's result on a lone stream with the same budget, and no wait gives
-    up."""
+def test_two_budgeted_streams_run_eager_calls_together(budgets, first):
+    """Verify (72B layer, or 136 rows per KV head over a 20K-token cache: nine
+    row tiles in one workgroup) on one budgeted stream and verify + accept (7B
+    layer) on another, called eagerly, enqueued together and repeated: every
+    result equals the same call's result on a lone stream with the same
+    budget (none of these launches waits; see the next test)."""
     dev = torch.device("cuda", 0)
     w72, w7 = W.WORKLOADS["llava72b"], W.WORKLOADS["llava7b"]
     if first == "wide":
@@ -151,3 +167,47 @@ def test_two_budgeted_streams_run_waiting_calls_together(budgets, first):
         assert all(torch.equal(a, b) for a, b in zip(x2, r2))
     pv.set_stream_cu_budget(s1, 0)
     pv.set_stream_cu_budget(s2, 0)
+
+
+@pytest.mark.parametrize("budgets,ctx", [((224, 32), (12000, 3500)), ((128, 128), (7000, 6432))])
+def test_two_budgeted_streams_replay_waiting_graphs_together(budgets, ctx):
+    """A 72B layer's verify with mass captured on one budgeted stream and a 7B
+    layer's on another, both in the waiting form, replayed together: every
+    replay equals the eager call, no wait gives up, and the statistics records
+    are 0 again afterwards."""
+    dev = torch.device("cuda", 0)
+    runs = []
+    for (T, hq, hkv), budget, n in zip(((9, 64, 8), (6, 28, 4)), budgets, ctx):
+        inp = W.random_verify_inputs(1, T, hq, hkv, 128, [n], "bf16", seed=n)
+        args = [to_dev(x) for x in (inp.q, inp.k, inp.v, inp.ctx_len)]
+        s, ws = torch.cuda.Stream(), pv.Workspace(dev)
+        status = torch.zeros(1, dtype=torch.int32, device=dev)
+        pv.set_stream_cu_budget(s, budget)
+        torch.cuda.synchronize()
+        note(f"waiting graph: budget {budget}, {hq}/{hkv} heads, ctx {n}")
+        with torch.cuda.stream(s):
+            ref = [t.clone() for t in pv.verify_attn(*args, scale=inp.scale, max_ctx=n, ws=ws, status=status)]
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=s):
+            outs = pv.verify_attn(*args, scale=inp.scale, max_ctx=n, ws=ws, status=status)
+        assert _kernels(g) == WAITING
+        g.instantiate()
+        with torch.cuda.stream(s):
+            g.replay()
+        torch.cuda.synchronize()
+        assert int(status.item()) == 0
+        assert all(torch.equal(a, b) for a, b in zip(outs, ref))
+        runs.append((s, g, outs, ref, status, ws, args))
+    for rep in range(20):
+        note(f"waiting graphs on budgets {budgets} together, round {rep}")
+        for s, g, *_ in runs * 3:
+            with torch.cuda.stream(s):
+                g.replay()
+        torch.cuda.synchronize()
+        for _, _, outs, ref, status, ws, _ in runs:
+            assert int(status.item()) == 0
+            assert all(torch.equal(a, b) for a, b in zip(outs, ref))
+            assert not ws.buf[256 * 1024:768 * 1024].any()
+    for s, *_ in runs:
+        pv.set_stream_cu_budget(s, 0)

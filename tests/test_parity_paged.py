@@ -72,10 +72,10 @@ SHAPES = [
     (2, 9, 64, 8, 128, [1111, 700], 64),           # 72B head layout, 5 row tiles
     (2, 2, 8, 2, 64, [190, 1000], 32),             # D = 64
     (1, 32, 16, 2, 128, [700], 256),               # T = 32, pages larger than a chunk
-    (1, 3, 8, 8, 128, [20000], 32),                # chunks > 512 tokens: stream variant
-    (2, 9, 64, 8, 128, [40000, 25000], 128),       # stream variant, 5 row tiles, ragged
+    (1, 3, 8, 8, 128, [20000], 32),                # long chunks
+    (2, 9, 64, 8, 128, [40000, 25000], 128),       # long chunks, 5 row tiles, ragged
     (4, 9, 28, 4, 128, [100, 900, 3, 1500], 32),   # batch 4 ragged, empty chunks
-    (1, 17, 64, 8, 128, [20000], 32),              # wide variant (136 rows in one workgroup)
+    (1, 17, 64, 8, 128, [20000], 32),              # 9 row tiles in one workgroup
 ]
 
 

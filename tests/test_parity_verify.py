@@ -42,18 +42,18 @@ SHAPES = [
     (2, 1, 8, 2, 128, [257, 33], "bf16"),          # T = 1 (pre-verify)
     (1, 2, 8, 2, 64, [190], "bf16"),               # D = 64 bf16, T = 2
     (3, 4, 6, 3, 128, [0, 1, 31], "bf16"),         # only the verify block visible
-    (1, 3, 8, 8, 128, [20000], "bf16"),            # chunks > 512 tokens: stream variant
+    (1, 3, 8, 8, 128, [20000], "bf16"),            # long chunks: two passes over K
     (2, 3, 12, 4, 64, [77, 129], "f32"),           # fp32 path, D = 64, 3 row tiles
     (1, 4, 8, 1, 128, [333], "f32"),               # fp32 path, D = 128
     (1, 32, 16, 2, 128, [700], "bf16"),            # T = 32 (the maximum): 256 rows, 4 row groups
     (4, 9, 28, 4, 128, [100, 900, 3, 1500], "bf16"),  # batch 4 ragged, 7B head layout
-    (1, 9, 64, 8, 128, [40000], "bf16"),          # stream variant, 5 row tiles: K/V blocks through LDS
-    (1, 8, 64, 8, 128, [30000], "bf16"),          # stream variant, 4 row tiles
-    (2, 10, 16, 2, 64, [40000, 25000], "bf16"),   # stream variant, D = 64, 5 row tiles, ragged
-    (1, 17, 64, 8, 128, [20000], "bf16"),         # wide variant: 136 rows (9 tiles) in one workgroup
-    (1, 12, 64, 8, 128, [24000], "bf16"),         # wide variant, 6 row tiles (3 padding tiles)
-    (2, 16, 36, 4, 64, [30000, 9000], "bf16"),    # wide variant, D = 64, 144 rows, empty chunks
-    (3, 16, 36, 4, 128, [30000, 5000, 17000], "bf16"),  # wide variant, ragged batch 3: cross-XCD exchanges
+    (1, 9, 64, 8, 128, [40000], "bf16"),          # long chunks, 5 row tiles
+    (1, 8, 64, 8, 128, [30000], "bf16"),          # long chunks, 4 row tiles
+    (2, 10, 16, 2, 64, [40000, 25000], "bf16"),   # long chunks, D = 64, 5 row tiles, ragged
+    (1, 17, 64, 8, 128, [20000], "bf16"),         # 136 rows (9 tiles) in one workgroup
+    (1, 12, 64, 8, 128, [24000], "bf16"),         # 6 row tiles
+    (2, 16, 36, 4, 64, [30000, 9000], "bf16"),    # 9 tiles, D = 64, 144 rows, empty chunks
+    (3, 16, 36, 4, 128, [30000, 5000, 17000], "bf16"),  # 9 tiles, ragged batch of 3
 ]
 
 
@@ -112,12 +112,11 @@ def test_long_video_131k():
 
 @pytest.mark.parametrize("shape", [(1, 9, 64, 8, 128, [1111]), (4, 9, 28, 4, 128, [100, 900, 3, 1500]),
                                    (1, 3, 8, 8, 128, [20000]), (1, 17, 64, 8, 128, [20000])],
-                         ids=["resident-72B-heads", "resident-ragged-empty-chunks", "stream", "wide"])
+                         ids=["72B-heads", "ragged-empty-chunks", "long-chunks", "nine-tiles"])
 def test_without_mass_or_lse(shape):
     """Output alone (no mass, no lse): bit-identical to the full call's output
     (the mass and lse are by-products of the same arithmetic) and within the
-    bar against the oracle, after a run in which the later calls' waits would
-    hang or time out if an arrival were skipped."""
+    bar against the oracle."""
     B, T, Hq, Hkv, D, ctx = shape
     inp = W.random_verify_inputs(B, T, Hq, Hkv, D, ctx, "bf16", seed=sum(ctx) + 7)
     note(f"verify without mass/lse q{inp.q.shape} k{inp.k.shape} ctx={ctx}")
@@ -170,9 +169,8 @@ def test_workspace_reused_across_shapes():
 
 def test_one_workspace_across_call_kinds():
     """One zero-filled workspace serves verify and accept calls in any order:
-    verify's monotonic group counters (same-XCD and cross-XCD exchange
-    launches alike) and accept's counters that return to zero share its
-    synchronisation region without disturbing each other."""
+    verify's statistics records, accept's decisions and the data areas of both
+    share it without disturbing each other."""
     ws = pv.Workspace(torch.device("cuda", 0))
     status = torch.zeros(1, dtype=torch.int32, device="cuda")
     acc = W.make_accept_inputs(W.WORKLOADS["tiny"], batch=8, salt=11)
