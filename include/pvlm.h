@@ -17,7 +17,7 @@
  *                       pvlm_prefill_epilogue_cossim that layer's criterion
  *                       fused into the prefill layer's residual add
  *   pvlm_topk_select    Eq. (topk_selection): keep the top 1 - alpha fraction;
- *                       pvlm_uvprune_topk_mass with the MASS score in one launch
+ *                       pvlm_uvprune_topk_mass with the MASS score in one call
  *   pvlm_gather_kv      the draft's compact cache [V*, X] (Sec. 4.2, Stage I)
  *   pvlm_spec_accept    speculative-sampling accept/reject (Sec. 2.2) with the
  *                       bonus token of Suppl. B
@@ -41,7 +41,7 @@
  *     capacities passed alongside them.  A kernel that finds one out of range
  *     clamps it into range (so memory is never touched out of bounds) and, if
  *     `status` is non-NULL, ORs PVLM_DEV_RANGE into *status.
- *   - Outputs must not alias inputs.  Optional outputs may be NULL.
+ *   - Outputs must not alias inputs unless the call says so.  Optional outputs may be NULL.
  *   - Calls are re-entrant; a workspace buffer must not be shared by two calls
  *     in flight at the same time.  The library's only mutable state is the
  *     per-stream compute-unit budgets below and the fixed scratch of
@@ -58,16 +58,19 @@
  *     means no two such graphs in flight at once on different streams.
  *     Everything else (eager verify calls among it) never waits and may run
  *     beside anything: it only delays it.
- *   - Compute-unit budgets (pvlm_set_stream_cu_budget): verify calls on a
- *     stream with a budget of C compute units plan their grids for at most C
- *     workgroups (long-row top-k calls too).  Streams whose budgets sum to at
- *     most the device's compute units may then replay waiting graphs at the
- *     same time, since every workgroup of all of them fits at once (one
- *     workgroup per compute unit at most).
- *   - Workspaces: zero-fill a workspace once before its first use.  Its first
- *     1 MiB holds the words of the waits between workgroups, which every call
- *     leaves zero again, so one buffer (at least as large as each call
- *     requires) serves calls of any kind and shape in sequence.
+ *   - Compute-unit budgets (pvlm_set_stream_cu_budget): on a stream with a
+ *     budget of C compute units, long-row top-k calls and the launches of
+ *     verify calls that stream the cache take at most C workgroups, one per
+ *     compute unit (verify calls with more than C groups of a sequence's, a KV
+ *     head's query rows take more, and never wait).  Streams whose budgets sum
+ *     to at most the device's compute units may therefore replay waiting
+ *     graphs at the same time: every workgroup of all of them fits at once.
+ *     Other launches (accept, gather, rope, the sums that end a verify call)
+ *     are not limited; they wait for nothing and end by themselves.
+ *   - Workspaces: zero-fill a workspace once before its first use.  Verify's
+ *     waits use words of its first 1 MiB that every call leaves zero again, so
+ *     one buffer (at least as large as each call requires) serves calls of any
+ *     kind and shape in sequence.
  *   - Layouts are C-contiguous, innermost index last.  "bf16" is IEEE
  *     bfloat16 stored in 2 bytes.
  */
@@ -379,14 +382,15 @@ pvlm_status pvlm_topk_select(int B, int64_t m_cap, const int32_t* m, const int32
 
 /* ------------------------------------------------------------------------
  * pvlm_uvprune_topk_mass -- the MASS form of pvlm_uvprune_score followed by
- * pvlm_topk_select, in one launch: Eq. (average_similarity) over a criterion
+ * pvlm_topk_select, in one call: Eq. (average_similarity) over a criterion
  * stack, score[b,i] = crit_stack[L][b][i] - crit_stack[0][b][i] (one fp32
  * subtraction, as pvlm_uvprune_score(MASS) rounds it), then Eq.
  * (topk_selection) over those scores.  The kept indices equal those of the
  * two calls bit for bit.
  *   crit_stack [L+1][B][m_cap] fp32, L >= 1; m, k [B] int32 device;
  *   score      [B][m_cap] fp32 output or NULL (written as pvlm_uvprune_score
- *              writes it, 0 past m[b]);
+ *              writes it, 0 past m[b]); it may be crit_stack's first or last
+ *              row, which it then replaces;
  *   idx        [B][k_cap] int32 output, as pvlm_topk_select (may be NULL
  *              when k_cap = 0: then only the scores are written).
  * Workspace, limits and errors are pvlm_topk_select's

@@ -215,8 +215,8 @@ def _dt(t: torch.Tensor) -> int:
 class Workspace:
     """A zero-initialised device scratch buffer that grows on demand.
 
-    The library leaves its synchronisation words consistent after every call,
-    so one buffer can serve successive calls on one stream (not concurrent
+    The library leaves the words that it waits on zero after every call, so
+    one buffer can serve successive calls on one stream (not concurrent
     calls: give each stream its own workspace).  A buffer that is outgrown is
     kept alive, not freed: a graph captured earlier, or a call still running,
     may use it.
@@ -236,7 +236,7 @@ class Workspace:
 
 
 # Default workspaces, one per (call kind, device, stream): calls on different
-# streams never share counters or data.
+# streams never share records or data.
 _ws_cache = {}
 # Default status words, one per device (see synchronize()).
 _status_cache = {}
@@ -254,7 +254,7 @@ def _default_ws(kind: str) -> Workspace:
     ws = _ws_cache.get(key)
     if ws is None:
         # (under graph capture the buffer comes from the graph's pool and its
-        # zero fill replays with the graph, which leaves the counters consistent)
+        # zero fill replays with the graph, ahead of the call)
         ws = _ws_cache[key] = Workspace()
     return ws
 
@@ -570,7 +570,7 @@ def topk_select(score, m, k, k_cap: int, *, idx=None, ws=None, status=None):
 def uvprune_topk_mass(crit_stack, m, k, k_cap: int, *, score=None, want_score: bool = True,
                       idx=None, ws=None, status=None):
     """pvlm_uvprune_topk_mass: the MASS score crit_stack[L] - crit_stack[0]
-    ([L+1][B][m_cap] fp32) and its top-k in one launch.  Returns (score or
+    ([L+1][B][m_cap] fp32) and its top-k in one call.  Returns (score or
     None, idx)."""
     _need(crit_stack, "crit_stack", torch.float32)
     dev = crit_stack.device

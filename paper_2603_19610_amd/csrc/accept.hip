@@ -43,15 +43,15 @@ constexpr int kMaxRows = 65;                    // 2 * gamma + 1, gamma <= 32
 constexpr double kNearTie = 1e-9;
 constexpr double kNegInfD = -__builtin_huge_val();
 
-// Inputs, then sizes, then outputs and workspace: the argument loads merge
-// adjacent fields into wide scalar loads allocated (and spilled) as one
-// unit, so fields used at different times sit in separate runs.
 // What the accept tests of a batch row decided.
 struct Decision {
   int acc, tie;
   double pM, pZ, qM, qZ;
 };
 
+// Inputs, then sizes, then outputs and workspace: the argument loads merge
+// adjacent fields into wide scalar loads allocated (and spilled) as one
+// unit, so fields used at different times sit in separate runs.
 struct AArgs {
   const float* dl;
   const float* tl;

@@ -38,10 +38,11 @@ hipError_t allow_dynamic_lds(const void* kernel, int bytes);
 // dynamic LDS bytes) fit on the current device at once: the occupancy the
 // runtime reports per compute unit, but at most `per_cu_most` (the runtime does
 // not count registers that a waves-per-SIMD bound reserves beyond those used),
-// times the compute units (the stream's budget when it has one).  A launch whose workgroups wait on each other (verify
-// under stream capture) checks this before launching; that they do start
-// together then rests on the caller's contract: the device not shared, or the
-// budgets of overlapping streams within its compute units.
+// times the compute units (the stream's budget when it has one).  A launch
+// whose workgroups wait on each other (verify under stream capture) checks this
+// before launching; that they do start together then rests on the caller's
+// contract: the device not shared, or the budgets of overlapping streams within
+// its compute units.
 pvlm_status check_coresident(const void* kernel, int grid, int block, int lds, int per_cu_most,
                              hipStream_t stream);
 
@@ -61,23 +62,11 @@ __device__ __forceinline__ void dev_flag(int32_t* status, int bit) {
   if (status) __hip_atomic_fetch_or(status, bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Coherent (agent-scope) loads/stores for data exchanged between workgroups
-// that may sit on different XCDs.  Each XCD has its own L2; a plain load can
-// hit a stale line in the reader's L2 even after an acquire, so every read of
-// another workgroup's data goes through these (they are independent loads and
-// pipeline when issued back to back).
-__device__ __forceinline__ float ld_agent(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ double ld_agent(const double* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(double* p, double v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
+// Coherent (agent-scope) load and store of a pair that workgroups of one launch
+// exchange, which may sit on different XCDs.  Each XCD has its own L2; a plain
+// load can hit a stale line in the reader's L2 even after an acquire, so every
+// read of another workgroup's data goes through these (they are independent
+// loads and pipeline when issued back to back).
 __device__ __forceinline__ void st_agent(float2* p, float2 v) {
   __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, v),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -86,12 +75,6 @@ __device__ __forceinline__ float2 ld_agent(const float2* p) {
   const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_AGENT);
   return __builtin_bit_cast(float2, u);
-}
-__device__ __forceinline__ int ld_agent(const int* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_agent(int* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Upper bound on polls of an inter-workgroup wait (each poll sleeps ~64

@@ -15,12 +15,11 @@ struct DeviceInfo {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Every workspace starts with a fixed-size region whose words a call may rely
-// on: verify's statistics records that a captured launch waits on, from
-// kSyncVerifyOff, are 0 between calls.  Data areas after the region may hold
-// anything.  Accept keeps its decisions at kSyncAcceptOff (written before they
-// are read in every call); kSyncTopkOff bounds the records and, with the rest,
-// the batch and group counts that calls accept.
+// Every workspace starts with a fixed-size region.  Verify's statistics records
+// that a captured launch waits on, from kSyncVerifyOff to kSyncTopkOff, are 0
+// between calls; accept keeps its decisions at kSyncAcceptOff (written before
+// they are read in every call).  Nothing else of a workspace is relied on.
+// kSyncLine enters only limits on batches and groups that calls are held to.
 constexpr size_t kSyncRegion = 1024 * 1024;
 constexpr size_t kSyncVerifyOff = 256 * 1024;
 constexpr size_t kSyncTopkOff = 768 * 1024;

@@ -503,14 +503,13 @@ pvlm_status plan_topk(int B, int64_t m_cap, TPlan* p, hipStream_t stream, bool w
   DeviceInfo di;
   pvlm_status st = with_stream ? device_info(&di, stream) : device_info(&di);
   if (st != PVLM_OK) return st;
-  if (B > di.cus) return PVLM_ERR_UNSUPPORTED;
+  if (B > di.cus) return PVLM_ERR_UNSUPPORTED;  // the documented limit: long rows for every compute unit
   const int nw_max = di.cus / B;  // every workgroup sums the others' histograms: no more than fill the device
   int64_t nw = (m_cap + kSlice - 1) / kSlice;
   if (nw > nw_max) nw = nw_max;
   if (nw < 1) nw = 1;
   p->NW = (int)nw;
   p->slice = (int)((m_cap + nw - 1) / nw);
-  if (kSyncLine * (size_t)B > kSyncAcceptOff - kSyncTopkOff) return PVLM_ERR_UNSUPPORTED;
   size_t off = kSyncRegion;
   p->off_hist = off;
   off = align_up(off + sizeof(int) * 4 * (size_t)B * p->NW * 256, 256);

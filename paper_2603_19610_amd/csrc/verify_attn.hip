@@ -150,16 +150,13 @@ struct Bf16 {
   typedef uint16_t E;
   static constexpr int D = D_, BLK = 32, TT = 2, DPL = D / 16, CH = D / 8;
   static constexpr int KS = D / 32;  // 16-byte chunks of a row per lane (chunk 4 ks + gq)
-  struct K {
-    uint4 r[TT][KS];
-  };
   // B operands of P.V: element s of r[jd] is V[token(s)][16 jd + n], tokens
   // {4 gq .. +3, 16 + 4 gq .. +3}
   struct V {
     bf16x8 r[DPL];
   };
   static constexpr bool kSwizzleV = true;
-  // cache row tb + row (row < 32) for a 16-byte piece, clamped like load_k
+  // cache row te, from which rows te .. te + BLK - 1 are contiguous (rows of the block at tb)
   static __device__ __forceinline__ const E* block(const KvRows& kv, int tb, int c1, int& te) {
     return kv_block<D>(kv, tb, c1, te);
   }
@@ -205,18 +202,10 @@ struct F32 {
   typedef float E;
   static constexpr int D = D_, BLK = 16, TT = 1, DPL = D / 16, CH = D / 4;
   static constexpr int KS = D / 16;
-  struct K {
-    uint4 r[TT][KS];
-  };
   struct V {
     float4 r[4][DPL / 4];
   };
   static constexpr bool kSwizzleV = false;
-  static __device__ __forceinline__ void load_k(const KvRows& kv, int tb, int c1, int n, int gq, K& k) {
-    const float* p = reinterpret_cast<const float*>(kv.base) + (size_t)min(tb + n, c1 - 1) * D + 4 * gq;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) k.r[0][ks] = *reinterpret_cast<const uint4*>(p + 16 * ks);
-  }
   static __device__ __forceinline__ const E* block(const KvRows& kv, int tb, int c1, int& te) {
     te = 0;
     return reinterpret_cast<const float*>(kv.base);
@@ -618,12 +607,12 @@ __attribute__((amdgpu_waves_per_eu(PartShape<M, RT>::kWpe, PartShape<M, RT>::kWp
       z = z * f0 + o[1] * f1;
       ref = Mx;
       floatx4 g0, g1;
-  #pragma unroll
+#pragma unroll
       for (int i = 0; i < 4; ++i) {
         g0[i] = __shfl(f0, 4 * gq + i, 64);
         g1[i] = __shfl(f1, 4 * gq + i, 64);
       }
-  #pragma unroll
+#pragma unroll
       for (int jd = 0; jd < DPL; ++jd) O[jd] = O[jd] * g0 + xo[jd * 64 + lane] * g1;
     }
   }

@@ -55,6 +55,8 @@ inline size_t workspace_bound(bool bf16, int B, int Hkv, int D, int RTT, int64_t
     if (!di.budgeted) W = 2 * di.cus;
     layout();
   }
+  // the limits of earlier plans, which kept a line of counters per group and
+  // per chunk in the fixed region: no call is taken beyond them
   *ok = 3 * kSyncLine * (size_t)groups <= kSyncTopkOff - kSyncVerifyOff &&
         kSyncLine * (size_t)B * splits <= kSyncVerifyOff;
   const size_t rows = (size_t)RT * 16;
