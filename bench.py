@@ -41,7 +41,7 @@ METRIC = "verify+prune step us/layer & achieved HBM TB/s, LLaVA-OV-72B layer sha
 HBM_PEAK_GBS = 8000.0
 PROFILES = os.path.join(ROOT, "profiles")
 VERIFY_SRCS = [os.path.join(ROOT, "paper_2603_19610_amd", "csrc", f)
-               for f in ("verify_attn.hip", "common.h")]
+               for f in ("verify_attn.hip", "verify_plan.h", "common.h")]
 COPY_BYTES = 512 << 20
 OTHER_CONFIGS = ("tiny", "llava7b", "llava72b", "qwen32b", "long")
 
@@ -132,7 +132,7 @@ def measured_traffic():
 
 
 def kernel_code_digest():
-    """sha256 of verify_attn.hip + common.h with comments and blank lines
+    """sha256 of verify_attn.hip, verify_plan.h and common.h with comments and blank lines
     stripped: changes whenever the verify kernel's code does."""
     cur = hashlib.sha256()
     for f in VERIFY_SRCS:
@@ -740,45 +740,38 @@ def overlap_record(torch, pv, W, dev, gamma=5, reps=50):
     return rec
 
 
-def verify_plan(w, cus=256, xcds=8):
+def verify_plan(w, cus=256):
     """The verify launch plan the library picks for this shape: (row tiles per
-    workgroup, row groups, splits, chunk tokens, resident, wide).  One
-    workgroup per CU; rows split into groups of at most 5 tiles, more groups
-    when the (batch, KV head) pairs are fewer than the XCDs; resident scores
-    for chunks of at most 512 tokens; one group of 9 tiles (wide variant, two
-    workgroups per CU) in place of two groups for streamed chunks."""
+    workgroup, row groups, chunks, tokens of a chunk, stages whose scores stay
+    in registers under capture, 0 for two passes over K).  At most nine
+    16-row tiles a workgroup, as many chunks as fit the compute units beside
+    the other groups', whole stages of 64 tokens (fp32: 32), two at least;
+    six tiles at most where that keeps a chunk resident."""
     rtt = -(-w.group * w.T // 16)
+    tokens = 64 if w.dtype == "bf16" else 32
     n = int(w.lengths().max()) + w.T
+    nst, heads = -(-n // tokens), w.batch * w.hkv
 
-    def layout(rg, slots=cus):
-        per_launch = min(w.batch * w.hkv * rg, slots)
-        splits = max(1, slots // per_launch)
-        chunk = -(-(-(-n // splits)) // 32) * 32
-        return per_launch, -(-n // chunk), chunk
+    def stages(rg):
+        return max(2, -(-nst // max(1, cus // (heads * rg))))
 
-    rg = -(-rtt // 5)
-    if w.batch * w.hkv * rg < xcds and rtt > rg:
-        rg = min(-(-xcds // (w.batch * w.hkv)), rtt)
-    rt = -(-rtt // rg)
-    per_launch, splits, chunk = layout(rg)
-    resident = chunk <= 512
-    wide = not resident and 5 < rtt <= 9 and w.batch * w.hkv >= xcds
-    if wide:  # two workgroups per CU
-        rg, rt = 1, 9
-        per_launch, splits, chunk = layout(rg, 2 * cus)
-    return rt, rg, per_launch, splits, chunk, resident, wide
+    rg, rg6 = -(-rtt // 9), -(-rtt // 6)
+    if -(-rtt // rg) > 6 and heads * rg6 <= cus and stages(rg6) <= 7:
+        rg = rg6
+    rt, st = -(-rtt // rg), stages(rg)
+    splits = -(-n // (st * tokens))
+    most = 20 if rt == 1 else 12 if rt == 2 else 7 if rt <= 6 else 0
+    fits = heads * rg * splits <= cus and heads * rtt * splits <= 4096
+    resident = next((r for r in (2, 7, most) if st <= r), 0) if st <= most and fits else 0
+    return rt, rg, splits, st * tokens, resident
 
 
-def verify_kernel_label(w, cus=256, xcds=8):
-    """The verify kernel variant of the launch plan (same-XCD exchange when
-    every group's workgroups share an XCD)."""
-    rt, rg, per_launch, splits, chunk, resident, wide = verify_plan(w, cus, xcds)
-    grid = -(-per_launch * splits // 8) * 8
-    local = grid % xcds == 0 and (grid // xcds) % splits == 0
-    where = "same-XCD" if local else "cross-XCD"
-    if wide:
-        return f"verify_wide_kernel<{w.head_dim},{where}>"
-    return f"verify_mfma_kernel<{w.head_dim},{rt},{'resident' if resident else 'stream'},{where}>"
+def verify_kernel_label(w, cus=256):
+    """The kernels of a captured verify call with mass."""
+    rt, _, _, _, res = verify_plan(w, cus)
+    t = f"{'Bf16' if w.dtype == 'bf16' else 'F32'}<{w.head_dim}>"
+    mass = "" if res else f" + verify_mass_kernel<{t},{rt}>"
+    return f"verify_part_kernel<{t},{rt},{res}>{mass} + verify_finish_kernel<{t}>"
 
 
 def teardown(torch, pv, *objs):
@@ -847,8 +840,8 @@ def main():
 
     if args.verify_only:
         # the launches as the bench times them: one graph of N verify
-        # launches (one per layer, cycling), replayed once; captured without
-        # an eager run, so the process makes no cooperative launch
+        # calls (one per layer, cycling), replayed once; captured without an
+        # eager run
         st.ws_v.get(pv.verify_attn_workspace_size(
             pv.PVLM_BF16 if w.dtype == "bf16" else pv.PVLM_F32, w.batch, w.T, w.hq, w.hkv,
             w.head_dim, w.n_cap(), st.max_ctx))
@@ -916,8 +909,8 @@ def main():
     if graph_used:
         stages = stage_times(torch, st, reps)
         k_mean = stages["verify"]
-    # one eager (cooperative) launch at a time behind a busy stream: the
-    # per-launch cost a caller outside a graph sees
+    # one eager call at a time behind a busy stream: the cost a caller outside
+    # a graph sees (its mass is a second pass over K)
     blocker = torch.randn((4096, 4096), device=dev, dtype=torch.bfloat16)
     n_eager = 40
     evs = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))

@@ -9,6 +9,9 @@
 //                                   limit, to the longest cache
 //   verify_plan_check sized         a workspace sized for the whole device is
 //                                   enough under every budget
+//   verify_plan_check show DT B T HQ HKV D N_CAP CTX
+//                                   prints a call's row tiles, row groups,
+//                                   chunks and tokens of a chunk
 // Prints the first failures and their number.
 #include <cstdio>
 #include <cstdlib>
@@ -103,6 +106,17 @@ int main(int argc, char** argv) {
              VSplit w;
              return split_verify(c.dt, c.B, c.T, c.Hq, c.Hkv, c.D, c.n_cap, c.ctx, whole, whole, &w) == PVLM_OK && p.bytes > w.bytes;
            }) != 0;
+  }
+  if (argc == 10 && !std::strcmp(argv[1], "show")) {
+    int64_t v[8];
+    for (int i = 0; i < 8; ++i) v[i] = std::atoll(argv[2 + i]);
+    DeviceInfo di;
+    di.cus = 256;
+    di.xcds = 8;
+    VSplit p;
+    if (split_verify((pvlm_dtype)v[0], v[1], v[2], v[3], v[4], v[5], v[6], v[7], di, di, &p) != PVLM_OK) return 1;
+    std::printf("%d %d %d %d\n", p.RT, p.RG, p.splits, p.chunk);
+    return 0;
   }
   return 2;
 }

@@ -25,6 +25,7 @@ def check(tmp_path_factory):
     def run(*args):
         r = subprocess.run([exe, *map(str, args)], capture_output=True, text=True, timeout=300)
         assert r.returncode == 0, r.stdout + r.stderr
+        return r.stdout
     return run
 
 
@@ -76,3 +77,16 @@ def test_workspace_size_holds_under_every_budget(check):
     """pvlm_verify_attn_workspace_size knows no stream: its answer has to do on
     streams with any compute-unit budget."""
     check("sized")
+
+
+def test_bench_names_the_plan_the_library_picks(check):
+    import sys
+    sys.path.insert(0, ROOT)
+    import bench
+    import workloads as W
+    for name, w in W.WORKLOADS.items():
+        got = check("show", int(w.dtype == "bf16"), w.batch, w.T, w.hq, w.hkv, w.head_dim, w.n_cap(),
+                    int(w.lengths().max()))
+        assert tuple(map(int, got.split())) == bench.verify_plan(w)[:4], name
+    assert bench.verify_kernel_label(W.WORKLOADS["llava72b"]) == \
+        "verify_part_kernel<Bf16<128>,5,7> + verify_finish_kernel<Bf16<128>>"
