@@ -15,11 +15,10 @@
 // picks that digit and histograms its own slice's next one; the last emits.
 // Each workgroup also counts its slice's keys above each digit, so the last
 // launch knows where every slice's output starts.  No workgroup waits for
-// another: one launch with five waits took 33.6 us for 131072 scores (the
-// waits) and a cooperative launch's own time when eager; with its gather
-// 60.1 us a pass eagerly and 42.0 captured, these 43.6 and 43.8.  (The slice
-// requested before the digit is known: 46.6, its loads then delay the
-// histograms'.)
+// another.  131072 scores from two criteria, us: one launch with five waits 51.1
+// eagerly (cooperative) and 38.0 captured, these 32.4 and 36.8; plain scores
+// 47.7 and 34.9, 31.6 and 36.9.  (The slice requested before the digit is known
+// was slower: its loads delay the histograms'.)
 #include "common.h"
 
 namespace pvlm {

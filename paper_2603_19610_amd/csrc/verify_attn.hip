@@ -32,18 +32,23 @@
 //    KV heads' partials.  Every order of summation is fixed.
 //  * fp32 inputs run the same kernels on v_mfma_f32_16x16x4_f32.
 //
-// What bounds it (one MI355X; HBM streams at 5.1-5.4 TB/s): long contexts are
-// bound by HBM (partial kernel, batch of four at 16-33K tokens, 419 MB: 74-82
-// us), 136 rows per KV head by the waves' LDS reads and issue (131K tokens:
-// 120 us of 105), short ones by the launches' own chain of memory round trips
-// (~1.7 us a launch, ~1 us a trip).  Rotary append and verify, us a layer,
-// against one waiting launch per call with statistics and O exchanges:
-//   64 x 8 heads, 9 rows, 12.8K tokens (captured)  30.5 -> 27.1
-//   28 x 4 heads, 6 rows, 6.4K (captured)          20.1 -> 18.1
-//   28 x 4 heads, 1 row, 0.8K, no mass (captured)  13.5 -> 11.7
-//   40 x 8 heads, 9 rows, batch 4, 16-33K (eager)   151 -> 128
-//   64 x 8 heads, 17 rows, 131K (eager)             204 -> 197
-//   fp32, 32 x 8 heads, 1 row, batch 4 (captured)   186 -> 28
+// What bounds it (one MI355X; a large copy streams at 5.1 TB/s): long contexts
+// are bound by HBM, K read twice (batch of four at 16-33K tokens: partial kernel
+// 80 us for 419 MB, which the copy's rate takes 81; mass kernel 46), 136 rows
+// per KV head by the waves' LDS reads and issue (131K tokens: partial 124 us
+// where the copy's rate takes 105, mass 74), short ones by the launches' own
+// chain of memory round trips (~1.7 us a launch, ~1 us a trip).  Rotary append
+// and verify, us a layer, against one waiting launch per call with statistics
+// and O exchanges, both timed in turn:
+//   64 x 8 heads, 9 rows, 12.8K tokens (captured)  30.7 -> 27.7
+//   28 x 4 heads, 6 rows, 6.4K (captured)          20.2 -> 18.5
+//   28 x 4 heads, 1 row, 0.8K, no mass (captured)  14.0 -> 11.6
+//   40 x 8 heads, 9 rows, batch 4, 16-33K (eager)   154 -> 141
+//   64 x 8 heads, 17 rows, 131K (eager)             214 -> 208
+//   4 x 1 heads, fp32, 5 rows, 1K (eager)            54 -> 33
+// Past seven stages a chunk (three to six row tiles) a captured call reads K
+// twice as well: the first line's layer takes 25.3 us without its append at
+// 14300 tokens, 30.5 at 14400.
 #include <mutex>
 #include <type_traits>
 
@@ -796,9 +801,9 @@ __device__ void combine_row(const VArgs& a, int64_t id) {
 #pragma unroll
   for (int j = 0; j < kU; ++j) v[j] = op[min(sg + j * SG, nsp - 1) * os];
   // the statistics of 256 chunks at a time, all in flight together: few rows
-  // over many chunks are bound by this wave's round trips (63K tokens, 18
-  // rows, 247 chunks, us a layer with the rotary append: 24.1 with 64 at a
-  // time and a second read, 22.0 this way)
+  // over many chunks are bound by this wave's round trips (18 rows over 247
+  // chunks, us a layer with the rotary append: 24.1 with 64 at a time and a
+  // second read, 22.0 this way)
   constexpr int kC = 4;
   float2 x[kC];
   auto load_stats = [&](int s0) {

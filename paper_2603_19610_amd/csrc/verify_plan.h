@@ -16,7 +16,9 @@ constexpr int kMaxRT = 9;  // 16-row tiles per workgroup of the partial kernel
 // either head dim: their waves-per-SIMD bound makes them reserve a unit's
 // registers (two tiles reserve 176 of a lane's 512 for each of six waves), and
 // at D = 128 their ring takes its LDS.  The runtime's occupancy figure counts
-// the registers they use, so a launch that waits has to go by this one.
+// the registers they use, so a launch that waits has to go by this one.  With
+// two planned at D = 64 a call ran in two rounds (18 rows over 63K tokens,
+// captured, us a layer: 18.7 without mass, against 14.6 with one).
 constexpr int kPerCu = 1;
 
 struct VSplit {
@@ -114,8 +116,9 @@ inline pvlm_status split_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   const int64_t nst = (n_plan + 2 * blk - 1) / (2 * blk), slots = (int64_t)di.cus * kPerCu;
   p->slots = (int)slots;
   // One workgroup per compute unit, all of them in one round (as many chunks as
-  // every group has compute units for: one workgroup more would run alone in a
-  // second round), and at least two stages each: fewer would only add partials.
+  // every group has compute units for: one workgroup more runs alone in a
+  // second round; batch of three, 8 KV heads, 16K tokens: 264 workgroups 82 us a
+  // layer, 240 68), and at least two stages each: fewer only add partials.
   auto chunk_stages = [&](int64_t groups) {
     const int64_t most = slots > groups ? slots / groups : 1, cs = (nst + most - 1) / most;
     return cs < 2 ? (int64_t)2 : cs;
