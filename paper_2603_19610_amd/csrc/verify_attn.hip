@@ -92,11 +92,16 @@ struct VArgs {
   float* lse;
   float* mass;
   int32_t* status;
-  int mass_wgs, comb_wgs;  // finish kernel: workgroups of each role
-  int64_t mass_pieces;     // ... and pieces of kFinThreads cache rows that the first share out
+  int mass_wgs;     // finish kernel: workgroups that sum the mass,
+  int mass_per;     // ... those of one sequence,
+  int mass_rows;    // ... and the cache rows of one
   bool o32;                // O partials are fp32
   bool clear;              // ... which also clears the statistics
 };
+
+// Three 64-byte lines: a fourth costs every launch's waves a scalar load more
+// before they start (208 bytes: 28 layers of one row over 0.8K tokens 333 us, 192: 324).
+static_assert(sizeof(VArgs) <= 192, "kernel arguments fit three lines");
 
 struct Unit {
   int split, bg, b, g, rg, ctx, N, c0, c1;
@@ -876,34 +881,34 @@ __device__ void combine_row(const VArgs& a, int64_t id) {
 
 // The mass of every cache row: the sum of its KV heads' and row groups'
 // partials in order (0 past the sequence).
-__device__ __forceinline__ void sum_mass(const VArgs& a, int64_t id) {
+__device__ __forceinline__ void sum_mass(const VArgs& a, int id) {
   constexpr int kP = 8;
   const int P = a.Hkv * a.RG;
-  const int64_t per = (a.n_cap + kFinThreads - 1) / kFinThreads;
-  const int b = (int)(id / per);
-  const int64_t t = (id - b * per) * kFinThreads + threadIdx.x;
-  if (t >= a.n_cap) return;
+  const int b = id / a.mass_per;
+  const int64_t t0 = (int64_t)(id - b * a.mass_per) * a.mass_rows;
   const int N = seq_ctx(a, b, false) + a.T;
   const float* mp = a.mpart + (size_t)b * P * a.n_cap;
-  float sum = 0.f;
-  if (t < N)
-    for (int p0 = 0; p0 < P; p0 += kP) {
-      float v[kP];
+  float* mass = a.mass + (size_t)b * a.n_cap;
+  for (int64_t t = t0 + threadIdx.x; t < min(t0 + a.mass_rows, a.n_cap); t += kFinThreads) {
+    float sum = 0.f;
+    if (t < N)
+      for (int p0 = 0; p0 < P; p0 += kP) {
+        float v[kP];
 #pragma unroll
-      for (int j = 0; j < kP; ++j) v[j] = mp[(size_t)min(p0 + j, P - 1) * a.n_cap + t];
+        for (int j = 0; j < kP; ++j) v[j] = mp[(size_t)min(p0 + j, P - 1) * a.n_cap + t];
 #pragma unroll
-      for (int j = 0; j < kP; ++j)
-        if (p0 + j < P) sum += v[j];
-    }
-  a.mass[(size_t)b * a.n_cap + t] = sum;
+        for (int j = 0; j < kP; ++j)
+          if (p0 + j < P) sum += v[j];
+      }
+    mass[t] = sum;
+  }
 }
 
 template <typename M>
 __global__ void __launch_bounds__(kFinThreads) verify_finish_kernel(VArgs a) {
   const int id = blockIdx.x;
-  if (id < a.mass_wgs) {
-    for (int64_t i = id; i < a.mass_pieces; i += a.mass_wgs) sum_mass(a, i);
-  } else if (a.o32) combine_row<M, float>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
+  if (id < a.mass_wgs) sum_mass(a, id);
+  else if (a.o32) combine_row<M, float>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
   else combine_row<M, typename M::E>(a, (int64_t)(id - a.mass_wgs) * kFinWaves + (threadIdx.x >> 6));
 }
 
@@ -1054,9 +1059,10 @@ pvlm_status verify_run(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int6
   a.units = B * Hkv * p.RG * p.splits;
   a.sl2 = scale * kLog2e;
   a.o32 = p.o32;
-  a.mass_wgs = mass ? mass_workgroups(B, n_cap) : 0;
-  a.mass_pieces = mass_pieces(B, n_cap);
-  a.comb_wgs = (B * Hkv * p.R + kFinWaves - 1) / kFinWaves;
+  a.mass_rows = (int)mass_rows(B, n_cap);
+  a.mass_per = (int)mass_workgroups(n_cap, a.mass_rows);
+  a.mass_wgs = mass ? B * a.mass_per : 0;
+  const int comb_wgs = (B * Hkv * p.R + kFinWaves - 1) / kFinWaves;
   // While a stream is captured, a call whose chunks' scores stay in registers
   // is one waiting launch; otherwise the mass is a second pass over K.
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1084,7 +1090,7 @@ pvlm_status verify_run(pvlm_dtype dt, int B, int T, int Hq, int Hkv, int D, int6
       PVLM_HIP(hipLaunchKernel(mk, grid, block, args, p.mass_lds, stream));
     }
   }
-  PVLM_HIP(hipLaunchKernel(reinterpret_cast<const void*>(p.finish), dim3(a.mass_wgs + a.comb_wgs),
+  PVLM_HIP(hipLaunchKernel(reinterpret_cast<const void*>(p.finish), dim3(a.mass_wgs + comb_wgs),
                            dim3(kFinThreads), args, 0, stream));
   return PVLM_OK;
 }

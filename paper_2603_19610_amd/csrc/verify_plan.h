@@ -78,16 +78,16 @@ inline pvlm_status check_verify(pvlm_dtype dt, int B, int T, int Hq, int Hkv, in
   return (int64_t)(Hq / Hkv) * T > 640 ? PVLM_ERR_UNSUPPORTED : PVLM_OK;
 }
 
-// Finish kernel: workgroups that sum the mass, each kFinThreads cache rows at a
-// time.  They take the rest of a long row in turn: with one workgroup for every
-// kFinThreads rows a launch would pass the 2^32 threads that it may hold.
+// Finish kernel: cache rows whose mass one workgroup sums, and the workgroups of
+// a sequence.  kFinThreads rows each, unless that takes more workgroups than
+// kMassWgs in all: a launch holds fewer than 2^32 threads.
 constexpr int kFinThreads = 256;
 constexpr int64_t kMassWgs = 1 << 16;
-inline int64_t mass_pieces(int B, int64_t n_cap) { return B * ((n_cap + kFinThreads - 1) / kFinThreads); }
-inline int mass_workgroups(int B, int64_t n_cap) {
-  const int64_t n = mass_pieces(B, n_cap);
-  return (int)(n < kMassWgs ? n : kMassWgs);
+inline int64_t mass_rows(int B, int64_t n_cap) {
+  const int64_t wgs = B < kMassWgs ? kMassWgs / B : 1, rows = (n_cap + wgs - 1) / wgs;
+  return (rows + kFinThreads - 1) / kFinThreads * kFinThreads;
 }
+inline int64_t mass_workgroups(int64_t n_cap, int64_t rows) { return (n_cap + rows - 1) / rows; }
 
 // The plan on a device, or on a stream's budget `di` of a device `whole`, for
 // arguments that check_verify takes.

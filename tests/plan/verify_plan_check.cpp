@@ -91,9 +91,11 @@ int main(int argc, char** argv) {
     long fail = 0;
     for (int B : {1, 3, 4, 64, 2048})
       for (int64_t n_cap : {(int64_t)1, (int64_t)256, (int64_t)257, (int64_t)1 << 24, ((int64_t)1 << 30) - 1, (int64_t)1 << 30}) {
-        const int64_t wgs = mass_workgroups(B, n_cap), rows = (int64_t)640 * 2048;  // rows of O, four a workgroup
-        fail += wgs < 1 || wgs > mass_pieces(B, n_cap) || (wgs + rows / 4) * kFinThreads >= (int64_t)1 << 32 ||
-                mass_pieces(B, n_cap) * kFinThreads < B * n_cap;
+        const int64_t per = mass_rows(B, n_cap), wgs = mass_workgroups(n_cap, per);
+        const int64_t rows = (int64_t)640 * 2048;  // rows of O, four a workgroup
+        fail += per % kFinThreads != 0 || per * wgs < n_cap || per * (wgs - 1) >= n_cap ||
+                (n_cap * B <= kMassWgs * kFinThreads && per != kFinThreads) ||
+                (B * wgs + rows / 4) * kFinThreads >= (int64_t)1 << 32;
       }
     std::printf("%ld grids fail\n", fail);
     return fail != 0;
