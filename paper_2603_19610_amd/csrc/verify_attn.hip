@@ -35,8 +35,8 @@
 // What bounds it (one MI355X; a large copy streams at 5.1 TB/s): long contexts
 // are bound by HBM, K read twice (batch of four at 16-33K tokens: partial kernel
 // 80 us for 419 MB, which the copy's rate takes 81; mass kernel 46), 136 rows
-// per KV head by the waves' LDS reads and issue (131K tokens: partial 124 us
-// where the copy's rate takes 105, mass 74), short ones by the launches' own
+// per KV head by the waves' LDS reads and issue (131K tokens: partial 124-128 us
+// where the copy's rate takes 105, mass 74-75), short ones by the launches' own
 // chain of memory round trips (~1.7 us a launch, ~1 us a trip).  Rotary append
 // and verify, us a layer, against one waiting launch per call with statistics
 // and O exchanges, both timed in turn:
