@@ -104,7 +104,7 @@ def test_default_workspaces_are_per_stream():
         assert torch.equal(o[0], ref[0]) and torch.equal(o[1], ref[1]) and torch.equal(o[2], ref[2])
 
 
-@pytest.mark.parametrize("budgets,first", [((224, 32), "72b"), ((128, 128), "72b"), ((224, 32), "wide")])
+@pytest.mark.parametrize("budgets,first", [((224, 32), "72b"), ((128, 128), "72b"), ((224, 32), "nine-tiles")])
 def test_two_budgeted_streams_run_eager_calls_together(budgets, first):
     """Verify (72B layer, or 136 rows per KV head over a 20K-token cache: nine
     row tiles in one workgroup) on one budgeted stream and verify + accept (7B
@@ -113,7 +113,7 @@ def test_two_budgeted_streams_run_eager_calls_together(budgets, first):
     budget (none of these launches waits; see the next test)."""
     dev = torch.device("cuda", 0)
     w72, w7 = W.WORKLOADS["llava72b"], W.WORKLOADS["llava7b"]
-    if first == "wide":
+    if first == "nine-tiles":
         a_in = W.random_verify_inputs(1, 17, 64, 8, 128, [20000], "bf16", seed=5)
     else:
         a_in = W.make_verify_inputs(w72, layer=1)
@@ -150,7 +150,7 @@ def test_two_budgeted_streams_run_eager_calls_together(budgets, first):
         r2 = [t.clone() for t in run2()]
     torch.cuda.synchronize()
     assert int(st1.item()) == 0 and int(st2.item()) == 0
-    if first == "wide":
+    if first == "nine-tiles":
         ro, rl, rm = oracle.verify_attn(f64(a_in.q, "bf16"), f64(a_in.k, "bf16"), f64(a_in.v, "bf16"),
                                         a_in.ctx_len, a_in.scale)
         assert_out(to_host_f64(r1[0]), ro)
